@@ -41,29 +41,29 @@ EXPERT_SHAPES = ((2048, 768, 64), (1536, 1024, 32), (1040, 1440, 96))
 def listed():
     return [
         # one sequence decoding: 24 layers' down-projections, row-major calls
-        dict(name="decode step, 1 row", kind="step", M=1, N=2560, K=9728, k=256, packed=False, layers=24),
+        dict(name="decode step 1 row", kind="step", M=1, N=2560, K=9728, k=256, packed=False, layers=24),
         # a batch of 40 sequences decoding (an odd number of row blocks), packed calls
-        dict(name="decode step, 40 rows", kind="step", M=40, N=2560, K=9728, k=256, packed=True, layers=24),
+        dict(name="decode step 40 rows", kind="step", M=40, N=2560, K=9728, k=256, packed=True, layers=24),
         # 64 tokens decoding through 4 expert layers: weight streaming
-        dict(name="expert decode, 64 tokens", kind="experts_step", tokens=64, N=2048, K=768, k=64,
+        dict(name="expert decode 64 tokens", kind="experts_step", tokens=64, N=2048, K=768, k=64,
              packed=False, layers=4),
         # one chunk of a chunked prefill
-        dict(name="prefill chunk, 512 rows", kind="linear", M=512, N=2560, K=9728, k=256, packed=True),
+        dict(name="prefill chunk 512 rows", kind="linear", M=512, N=2560, K=9728, k=256, packed=True),
         # a ragged prompt through the row-major pair, K + k not a multiple of 128
-        dict(name="ragged prompt, 1537 rows", kind="linear", M=1537, N=2560, K=4096, k=96, packed=False),
+        dict(name="ragged prompt 1537 rows", kind="linear", M=1537, N=2560, K=4096, k=96, packed=False),
         # a prompt through a wide short-K projection (gate / up): the output is most of the bytes
-        dict(name="wide projection, 4096 rows", kind="linear", M=4096, N=9728, K=2560, k=64, packed=True),
+        dict(name="wide projection 4096 rows", kind="linear", M=4096, N=9728, K=2560, k=64, packed=True),
         # a long prompt's down-projection: the largest matrix product
-        dict(name="down projection, 8192 rows", kind="linear", M=8192, N=2560, K=9728, k=256, packed=True),
+        dict(name="down projection 8192 rows", kind="linear", M=8192, N=2560, K=9728, k=256, packed=True),
         # a 4096-token prompt through the experts
-        dict(name="expert prefill, 4096 tokens", kind="experts", tokens=4096, N=2048, K=768, k=64,
+        dict(name="expert prefill 4096 tokens", kind="experts", tokens=4096, N=2048, K=768, k=64,
              packed=True),
         # the gated activation of a long prompt (offline copy), then the down-projection
-        dict(name="gated activation, 8192 rows", kind="swiglu", M=8192, N=2560, K=9984, packed=True),
+        dict(name="gated activation 8192 rows", kind="swiglu", M=8192, N=2560, K=9984, packed=True),
         # the same row-major, a short ragged prompt
-        dict(name="gated activation, 333 rows", kind="swiglu", M=333, N=2560, K=4192, packed=False),
+        dict(name="gated activation 333 rows", kind="swiglu", M=333, N=2560, K=4192, packed=False),
         # calibrating one layer: three candidate alphas on 256 calibration rows
-        dict(name="alpha search, 3 candidates", kind="search", N=2560, K=9728, k=256, T=256, alphas=3),
+        dict(name="alpha search 3 candidates", kind="search", N=2560, K=9728, k=256, T=256, alphas=3),
         # loading a layer of experts
         dict(name="pack expert weights", kind="pack", E=128, N=2048, K=832),
     ]

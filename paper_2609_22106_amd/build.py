@@ -27,13 +27,14 @@ HIPCC = os.path.join(ROCM, "bin", "hipcc")
 HIP_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-mcode-object-version=5",
+    "-fconstexpr-steps=16777216",   # the SiLU table
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-munsafe-fp-atomics", "-Wall", "-Wno-unused-function",
 ]
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wall",
               "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include"]
 
-DEVICE_SOURCES = ["act_quant.hip", "pack.hip", "gemm_tile.hip", "gemm_stream.hip", "gemm_decode.hip",
+DEVICE_SOURCES = ["act_quant.hip", "swiglu_quant.hip", "pack.hip", "gemm_tile.hip", "gemm_stream.hip", "gemm_decode.hip",
                   "gemm_streamk.hip",
                   "evaluate.hip", "noalloc.hip"]
 HOST_SOURCES = ["prepare.cpp", "abi.cpp"]

@@ -66,6 +66,27 @@ __device__ __forceinline__ float quad_max(float x) {
   return x;
 }
 
+// A quad's 32-block, 8 values per lane -> the lane's word of 8 codes and the
+// block's scale code (in every lane).  t = z * 2^-e is exact (a power-of-two
+// product whose magnitude stays below 8, or a signed zero/denormal that encodes
+// as a signed zero either way); its E2M1 code comes from the hardware converter
+// at scale 1, which rounds to nearest even and saturates at 6 exactly like the
+// software rule on every float32 (checked exhaustively on the GPU).  Four
+// converts, each writing its pair into one byte of the word.
+__device__ __forceinline__ uint32_t quantize8(const float (&z)[8], uint32_t* scale) {
+  float amax = 0.0f;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) amax = fmaxf(amax, fabsf(z[j]));
+  const uint32_t code = e8m0_code(quad_max(amax));
+  const float mul = e8m0_reciprocal(code);
+  uint32_t w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(0u, z[0] * mul, z[1] * mul, 1.0f, 0);
+  w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, z[2] * mul, z[3] * mul, 1.0f, 1);
+  w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, z[4] * mul, z[5] * mul, 1.0f, 2);
+  w = __builtin_amdgcn_cvt_scalef32_pk_fp4_f32(w, z[6] * mul, z[7] * mul, 1.0f, 3);
+  *scale = code;
+  return w;
+}
+
 // One 16x16x128 block-scaled MFMA with FP4 (E2M1) A and B operands:
 //   C[i][j] += sum_{k<128} 2^(sa-127) A[i][k] * 2^(sb-127) B[k][j]
 // Lane l supplies A row (l % 16), K elements [32*(l/16), 32*(l/16)+32) as 16

@@ -342,6 +342,17 @@ size_t prq_tune_streamk_workspace_bytes(int M, int N, int K_aug, int num_cus, in
                          : 0;
 }
 
+// Tuning entry: the gated quantizer with SiLU computed (mode 1) or looked up (2).
+int prq_tune_swiglu_quant(const void* gate, const void* up, int64_t ld, int M, int K_aug, uint8_t* A,
+                          uint8_t* As, int packed, int mode, int num_cus, hipStream_t stream) {
+  if (M <= 0 || K_aug <= 0 || K_aug % 32 || ld < K_aug || ld % 8 || mode < 0 || mode > 2) return -1;
+  return prq::launch_swiglu_quant(static_cast<const uint16_t*>(gate), static_cast<const uint16_t*>(up),
+                                  ld, M, K_aug, A, As, packed != 0, num_cus, stream,
+                                  mode) == hipSuccess
+             ? 0
+             : -3;
+}
+
 // Tuning entry: the tile GEMM with an explicit tile shape (0, 1 or 2).
 int prq_tune_gemm_tile(const uint8_t* Aq, const uint8_t* Asc, int M, const int32_t* off, int E,
                        const uint8_t* Wp, const uint8_t* Wps, int N, int K_aug, float* Y, int shape,

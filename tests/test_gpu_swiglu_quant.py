@@ -124,3 +124,46 @@ def test_offline_copy_producer_side_end_to_end(M):
     Y_ref = pq.gemm(rq, rs, art["Wq"], art["Wsc"])
     assert_gemm_close(Y, Y_ref, f"producer side packed M={M}")
     assert_gemm_close(Y2, Y_ref, f"producer side row-major M={M}")
+
+
+def test_silu_lookup_equals_sequence_for_every_gate():
+    """The looked-up SiLU against the computed one and the oracle over every finite
+    bf16 gate, in order (a thread's gates all in the table or all outside), shuffled
+    (mixed) and scattered among gates of 1; row-major and packed."""
+    import ctypes
+    from paper_2609_22106_amd import build
+    prq = _prq()
+    lib = ctypes.CDLL(build.PROBE_LIB)
+    p = ctypes.c_void_p
+    fn = lib.prq_tune_swiglu_quant
+    fn.argtypes = [p, p, ctypes.c_int64, ctypes.c_int, ctypes.c_int, p, p, ctypes.c_int, ctypes.c_int,
+                   ctypes.c_int, p]
+    rng = np.random.default_rng(11)
+    K = 2048 + 32                       # not whole 128-element steps nor whole 512-element chunks
+    every = np.arange(65536, dtype=np.uint16)
+    finite = every[(every & 0x7FFF) < 0x7F80]
+    one = np.uint16(0x3F80)
+    rows = [finite, rng.permutation(finite), np.where(rng.random(finite.size) < 0.9, one, rng.permutation(finite))]
+    flat = np.concatenate(rows)
+    M = -(-flat.size // K)
+    g = np.resize(flat, (M, K)).astype(np.uint16)
+    u = np.where(rng.random((M, K)) < 0.5, one, np.uint16(0xBF80)).astype(np.uint16)
+    dg, du = dev(g), dev(u)
+    cb, sb = prq.prq_packed_act_bytes(M, K)
+    say("silu lookup case:", M, K)
+    for packed, nq, ns in ((0, M * K // 2, M * K // 32), (1, cb, sb)):
+        got = []
+        for mode in (1, 2):
+            A = torch.full((nq,), 0x5A, dtype=torch.uint8, device="cuda")
+            As = torch.full((ns,), 0xA5, dtype=torch.uint8, device="cuda")
+            st = fn(dg.data_ptr(), du.data_ptr(), K, M, K, A.data_ptr(), As.data_ptr(), packed, mode, 256,
+                    torch.cuda.current_stream().cuda_stream)
+            assert st == 0
+            torch.cuda.synchronize()
+            got.append((host(A), host(As)))
+        np.testing.assert_array_equal(got[0][0], got[1][0])
+        np.testing.assert_array_equal(got[0][1], got[1][1])
+        if not packed:
+            rq, rs = pq.swiglu_quant(g, u)
+            np.testing.assert_array_equal(got[1][0].reshape(M, -1), rq)
+            np.testing.assert_array_equal(got[1][1].reshape(M, -1), rs)

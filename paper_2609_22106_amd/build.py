@@ -34,7 +34,7 @@ HIP_FLAGS = [
 HOST_FLAGS = ["-O2", "-std=c++17", "-fPIC", "-ffp-contract=off", "-Wall",
               "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include"]
 
-DEVICE_SOURCES = ["act_quant.hip", "swiglu_quant.hip", "pack.hip", "gemm_tile.hip", "gemm_stream.hip", "gemm_decode.hip",
+DEVICE_SOURCES = ["act_quant.hip", "swiglu_quant.hip", "prepare_device.hip", "pack.hip", "gemm_tile.hip", "gemm_stream.hip", "gemm_decode.hip",
                   "gemm_streamk.hip",
                   "evaluate.hip", "noalloc.hip"]
 HOST_SOURCES = ["prepare.cpp", "abi.cpp"]

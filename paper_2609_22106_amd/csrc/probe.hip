@@ -342,6 +342,24 @@ size_t prq_tune_streamk_workspace_bytes(int M, int N, int K_aug, int num_cus, in
                          : 0;
 }
 
+// The device construction of one export from given scales (device pointers; rank
+// and err are scratch / column errors, maxima [2][K] float bits starting at 0).
+int prq_tune_prepare_device(const uint16_t* W, int N, int K, const uint16_t* X, int T, int k_tail,
+                            int search, const float* scale, const float* inv, uint32_t* maxima,
+                            double* err, int32_t* rank, int32_t* perm, float* scale_pos,
+                            float* inv_pos, uint8_t* Wq, uint8_t* Wsc, hipStream_t stream) {
+  if (N <= 0 || T <= 0 || K <= 0 || K % 32 || K > 16384 || k_tail < 0 || k_tail % 32 || k_tail > K) return -1;
+  if (prq::launch_channel_maxima(X, T, K, maxima, stream) != hipSuccess ||
+      prq::launch_channel_maxima(W, N, K, maxima + K, stream) != hipSuccess ||
+      prq::launch_tail_selection(W, N, K, k_tail, 1, scale, inv, err, rank, perm, scale_pos, inv_pos,
+                                 stream) != hipSuccess)
+    return -3;
+  return prq::launch_augment_weight(W, N, K, k_tail, perm, scale_pos, search != 0, Wq, Wsc, stream) ==
+                 hipSuccess
+             ? 0
+             : -3;
+}
+
 // Tuning entry: the gated quantizer with SiLU computed (mode 1) or looked up (2).
 int prq_tune_swiglu_quant(const void* gate, const void* up, int64_t ld, int M, int K_aug, uint8_t* A,
                           uint8_t* As, int packed, int mode, int num_cus, hipStream_t stream) {

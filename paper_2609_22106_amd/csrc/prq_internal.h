@@ -83,6 +83,25 @@ hipError_t launch_swiglu_quant(const uint16_t* G, const uint16_t* U, int64_t ld,
                                uint8_t* Aq, uint8_t* Asc, bool packed, int num_cus,
                                hipStream_t stream, int mode = 0);
 
+// prepare.cpp: the scales of Algorithm 1, step 3, from the channel maxima given as
+// float bits of their magnitudes (bf16 values): scale and inv_scale [K].
+void channel_scales(const uint32_t* a_bits, const uint32_t* b_bits, int K, double alpha,
+                    int scale_mode, float* scale, float* inv_scale);
+
+// prepare_device.hip: prq_prepare_ex's construction on the device (K <= 16384).
+// Column magnitudes' maxima as float bits (out [K] starts at 0).
+hipError_t launch_channel_maxima(const uint16_t* X, int rows, int K, uint32_t* out, hipStream_t stream);
+// For each of n_alpha rows of scale / inv [n_alpha][K]: column errors err, the
+// tail permutation and the scales and inverse scales in position order (all
+// [n_alpha][K]; rank is scratch).
+hipError_t launch_tail_selection(const uint16_t* W, int N, int K, int k_tail, int n_alpha,
+                                 const float* scale, const float* inv, double* err, int32_t* rank,
+                                 int32_t* perm, float* scale_pos, float* inv_pos, hipStream_t stream);
+// Canonical Wq [N][K_aug/2], Wsc [N][K_aug/32] of one alpha; search: the E8M0 search.
+hipError_t launch_augment_weight(const uint16_t* W, int N, int K, int k_tail, const int32_t* perm,
+                                 const float* scale_pos, bool search, uint8_t* Wq, uint8_t* Wsc,
+                                 hipStream_t stream);
+
 // pack.hip: the packed weight layout the GEMM kernels read.
 size_t packed_code_bytes(int N, int K_aug, int E);
 size_t packed_scale_bytes(int N, int K_aug, int E);

@@ -12,10 +12,10 @@
 // kBM/kWM x kBN/kWN).  Per 128-element K step both operands are staged in LDS
 // in MFMA lane order -- for each 16-row block, 64 lanes x 16 bytes, lane l
 // holding row l % 16, K part l / 16 -- so that every operand read of a wave is
-// one contiguous kilobyte (conflict-free 16-byte lane reads).  The weight comes
-// in that order already (packed layout, pack.hip) and is copied verbatim; the
-// activation rows are transposed into it on the store.  Scales are staged the
-// same way, one scale byte per lane in a dword slot.  Pipeline: kNS LDS
+// one contiguous kilobyte (conflict-free 16-byte lane reads).  The weight (and a
+// packed activation) comes in that order already (packed layout, pack.hip) and is
+// copied verbatim with its scales; row-major activation rows are copied 64 bytes
+// a step, their scales in windows of four steps.  Pipeline: kNS LDS
 // stages filled by direct global->LDS loads (global_load_lds: one wave
 // instruction writes one lane-ordered kilobyte), kNS - 1 K steps in flight; per
 // step each wave waits for its own loads of that step with an explicit vmcnt,
@@ -144,24 +144,23 @@ __device__ __forceinline__ void interleave() {
   });
 }
 
-// How the activation operand is laid out in memory: row-major Aq/Asc with the
-// scales staged a byte at a time or, when K_aug % 128 == 0, one aligned dword
-// per row and step; or the packed (weight) layout, staged like the weight.
-enum AMode { kARowByte = 0, kARowDword = 1, kAPacked = 2 };
+// How the activation operand is laid out in memory: row-major Aq/Asc (any K_aug,
+// any alignment of Asc), or the packed (weight) layout, staged like the weight.
+enum AMode { kARow = 0, kAPacked = 1 };
 
 // LDS stage of one 128-element K step: A codes [kBM/16 blocks][1 KiB] | B codes
 // [kBN/16 blocks][1 KiB] | A scales | B scales [kBN/16 tiles][64 dwords].  Codes
 // are in MFMA lane order (block b, lane l: row 16b + l % 16, K part l / 16, 16
-// bytes).  A scales: row dwords -- one dword per row (the row's four scale bytes
-// of the step); row bytes -- one byte per lane-order slot of each 16-row block
-// (dword slots); packed -- as B.  B scales are the packed weight's dwords of the
+// bytes); row-major A codes instead as 16 rows of 64 bytes, row r's K part p in
+// slot p ^ (r / 2) % 4.  A scales: packed as B; row-major not staged (each wave
+// loads its own into registers).  B scales are the packed weight's dwords of the
 // step's group of four steps (byte j = step 4q+j).
 template <int kBM, int kBN, int kAMode>
 struct TileStage {
   static constexpr int kABlk = kBM / 16, kBBlk = kBN / 16;
   static constexpr int kOffB = kABlk * 1024;
   static constexpr int kOffAs = (kABlk + kBBlk) * 1024;
-  static constexpr int kAsBytes = kAMode == kARowDword ? kBM * 4 : kABlk * 256;
+  static constexpr int kAsBytes = kAMode == kAPacked ? kABlk * 256 : 0;
   static constexpr int kOffBs = kOffAs + kAsBytes;
   static constexpr int kBytes = kOffBs + kBBlk * 256;
 };
@@ -175,7 +174,6 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
     const uint8_t* __restrict__ Wps, int N, int K_aug, float* __restrict__ Y, int splits,
     int split_steps, float* __restrict__ ws, int group_rows) {
   using L = TileStage<kBM, kBN, kAMode>;
-  constexpr bool kScaleDword = kAMode == kARowDword;
   constexpr bool kPackedA = kAMode == kAPacked;
   constexpr int kWaves = kWM * kWN;
   constexpr int kThreads = kWaves * 64;
@@ -189,20 +187,18 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
   // (256 x 320: 20 blocks, 8 waves) the last block is loaded again into its own
   // place (the same bytes), so that every wave issues the same loads.
   constexpr int kAPer = kABlk / kWaves, kBPer = (kBBlk + kWaves - 1) / kWaves;
-  // Scale instructions per step: A as 64 row dwords, one per 16-row block
-  // (bytes), or four block entries of 256 bytes (packed); B as four tile
-  // entries.  When there are fewer than waves, several waves load the same
-  // chunk (identical bytes).
-  constexpr int kAsChunks = kScaleDword ? kBM / 64 : (kPackedA ? kABlk / 4 : kABlk);
+  // Scale instructions per step: four block entries of 256 bytes (packed A, and
+  // B).  When there are fewer than waves, several waves load the same chunk
+  // (identical bytes).
+  constexpr int kAsChunks = kPackedA ? kABlk / 4 : 0;
   constexpr int kBsChunks = kBBlk / 4;
-  constexpr int kAsPer = (kAsChunks + kWaves - 1) / kWaves;
   constexpr int kBsPer = (kBsChunks + kWaves - 1) / kWaves;
   // Packed activations: the A and B scale chunks (a kilobyte each) are one list
   // dealt to the waves in turn, so no wave reloads a chunk another wave loads.
   constexpr int kScChunks = kAsChunks + kBsChunks;
   constexpr int kScPer = (kScChunks + kWaves - 1) / kWaves;
   // direct-to-LDS loads per wave per step
-  constexpr int kLoads = kAPer + kBPer + (kPackedA ? kScPer : kAsPer + kBsPer);
+  constexpr int kLoads = kAPer + kBPer + (kPackedA ? kScPer : kBsPer);
   static_assert(kNS >= 2 && kNS <= 4, "stages");
   static_assert(kNS * L::kBytes <= 160 * 1024, "LDS");
   static_assert(L::kBytes >= kThreads * 4 + 16, "the expert scan borrows a stage");
@@ -216,6 +212,10 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
   __shared__ __align__(16) uint8_t st1[L::kBytes];
   __shared__ __align__(16) uint8_t st2[kNS > 2 ? L::kBytes : 16];
   __shared__ __align__(16) uint8_t st3[kNS > 3 ? L::kBytes : 16];
+  // Row-major A: two windows of four steps' scale dwords ([step][row]).
+  constexpr int kWindow = kPackedA ? 16 : kBM * 16;
+  __shared__ __align__(16) uint8_t aw_lds[2 * kWindow];
+  static_assert(kNS * L::kBytes + 2 * kWindow <= 160 * 1024 + 32, "LDS");
   auto stage = [&](auto pc) -> uint8_t* {
     constexpr int p = decltype(pc)::value % kNS;
     if constexpr (p == 0) return st0;
@@ -282,7 +282,10 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: scalar registers
   const int wm = wave / kWN, wn = wave % kWN;
-  const int lr = lane & 15, lk = lane >> 4;
+  // Row-major A codes: 4 lanes load a row's 64 bytes of the step (16 half lines a
+  // wave instruction), their K parts permuted by the row so that the operand
+  // reads below meet every LDS bank once.
+  const int lr = lane >> 2, lk = (lane & 3) ^ ((lane >> 3) & 3);
 
   // Per-lane byte offsets of this wave's loads from uniform bases (fixed over
   // the K loop; rows and tiles clamped into the operands; the host checks that
@@ -294,7 +297,7 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
   // banks, so without the swap lanes 0-15 and 16-31 (same K part, two blocks)
   // hit the same 16 banks; with it they take the other 16.  A lane's global
   // source is its own piece's swap partner.
-  uint32_t a_off[kAPer], as_off[kAsPer], b_off[kBPer], bs_off[kBsPer], sc_off[kScPer];
+  uint32_t a_off[kAPer], b_off[kBPer], bs_off[kBsPer], sc_off[kScPer];
   const int swz = ((lane & 15) ^ (((lane >> 4) & 1) << 2)) * 16;
 #pragma unroll
   for (int i = 0; i < kAPer; ++i) {
@@ -305,13 +308,6 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
       const int m = min(row_begin + (wave + i * kWaves) * 16 + lr, row_end - 1);
       a_off[i] = static_cast<uint32_t>(m) * static_cast<uint32_t>(row_bytes) + lk * 16;
     }
-  }
-#pragma unroll
-  for (int i = 0; i < kAsPer; ++i) {
-    const int c = (wave + i * kWaves) % kAsChunks;
-    const int m = kScaleDword ? min(row_begin + c * 64 + lane, row_end - 1)
-                              : min(row_begin + c * 16 + lr, row_end - 1);
-    as_off[i] = static_cast<uint32_t>(m) * nb;
   }
 #pragma unroll
   for (int i = 0; i < kScPer; ++i) {   // packed: A chunks first, then B chunks
@@ -336,7 +332,7 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
   // multiple of 128, K parts of the last step past K_aug point at the row start
   // (they meet zero weight codes with finite scales).
   auto issue = [&](int s, uint8_t* st) {
-    const bool kok = kScaleDword || s * kStepK + lk * 32 < K_aug;
+    const bool kok = s * kStepK + lk * 32 < K_aug;
 #pragma unroll
     for (int i = 0; i < kAPer; ++i) {
       if constexpr (kPackedA)   // padded past K_aug and M: whole steps, whole blocks
@@ -362,19 +358,6 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
                                          PRQ_LPTR(st + dst), 16, 0, 0);
       }
     } else {
-#pragma unroll
-      for (int i = 0; i < kAsPer; ++i) {
-        const int c = (wave + i * kWaves) % kAsChunks;
-        if constexpr (kScaleDword)   // K_aug % 128 == 0: the row's 4 bytes of step s, aligned
-          __builtin_amdgcn_global_load_lds(PRQ_GPTR(Asc + (as_off[i] + s * 4)),
-                                           PRQ_LPTR(st + L::kOffAs + c * 256), 4, 0, 0);
-        else {   // block c: the lane's K part (swapped in odd blocks); past K_aug the row start
-          const int kp = lk ^ (c & 1);
-          __builtin_amdgcn_global_load_lds(
-              PRQ_GPTR(Asc + (as_off[i] + (s * kStepK + kp * 32 < K_aug ? s * 4 + kp : 0))),
-              PRQ_LPTR(st + L::kOffAs + c * 256), 1, 0, 0);
-        }
-      }
 #pragma unroll
       for (int i = 0; i < kBsPer; ++i) {
         const int c = (wave + i * kWaves) % kBsChunks;
@@ -405,23 +388,85 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
   // add compile-time constants (the instruction's immediate offset).
   const int blk_sel = (lane >> 4) & 1;
   const int lib0 = (lane & 15) + 16 * (lane >> 5);
-  const uint32_t a_lb = (wm * (kTM / 16) + blk_sel) * 1024 + lib0 * 16;
+  // Row-major A: row l % 16 of the block, slot of part 2h + l / 32 (h = 1 flips
+  // the slot's high bit).
+  const uint32_t a_row = (wm * (kTM / 16) + blk_sel) * 1024 + (lane & 15) * 64;
+  const int a_slot = (lane >> 5) ^ ((lane >> 1) & 3);
+  const uint32_t a_lb = kPackedA ? (wm * (kTM / 16) + blk_sel) * 1024 + lib0 * 16 : a_row + a_slot * 16;
+  const uint32_t a_lb1 = kPackedA ? a_lb + 512 : a_row + (a_slot ^ 2) * 16;
   const uint32_t b_lb = L::kOffB + (wn * (kTN / 16) + blk_sel) * 1024 + lib0 * 16;
   // Scale dwords: half h of a step reads K part 2h + l / 32, found in an odd
   // block (blk_sel = 1) at part 2h + (l / 32 ^ 1).
   static_assert((kTM / 16) % 2 == 0 && (kTN / 16) % 2 == 0, "blk_sel is the block parity");
   const uint32_t lsc = (lane & 15) * 4 + (((lane >> 5) ^ blk_sel) * 64);
-  const uint32_t as_lb = kScaleDword ? L::kOffAs + (wm * kTM + (lane & 31)) * 4
-                                     : L::kOffAs + (wm * (kTM / 16) + blk_sel) * 256 + lsc;
+  const uint32_t as_lb = L::kOffAs + (wm * (kTM / 16) + blk_sel) * 256 + lsc;
   const uint32_t bs_lb = L::kOffBs + (wn * (kTN / 16) + blk_sel) * 256 + lsc;
-  const uint32_t a_shift = 8 * (lane >> 5);   // row dword: part l / 32 to byte 0, 2 + l / 32 to byte 2
-  auto read = [&](const uint8_t* st, auto hc, Half& o) {
+  // Row-major A scales, a window of kU steps at a time, once per workgroup: 4
+  // lanes load a row's 16 bytes (byte j of a step's dword = K part j), through
+  // registers because a row starts at any byte: each lane takes the aligned dword
+  // of its step and the next one and puts the step's dword into LDS ([step][row]),
+  // two windows in turn.  A lane per row and step asks for a 128-byte line for 4
+  // bytes: with those loads 2048 x 2560 x 9984 in 128 x 128 tiles took 80 us (52
+  // with them left out), 1537 x 2560 x 4192 in 256 x 128 36 us, the planned 8192 x
+  // 2560 x 9984 182 us; now 52, 29 and 111.  (16 bytes of a row per lane, each wave
+  // for itself: 53 us at aligned rows, no gain at odd ones, which take the hardware
+  // as long as the dword a step.)  No load passes the last dword that holds a byte
+  // of Asc: lanes beyond it load earlier and pick the later dword.
+  constexpr int kSc = kPackedA ? 1 : kBM * 4 / kThreads;   // (row, step) entries per thread
+  const uint32_t as_lead = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(Asc) & 3u);
+  const uint8_t* const as_base = Asc - as_lead;
+  const uint32_t as_last = (as_lead + static_cast<uint32_t>(M) * nb - 1) & ~3u;
+  // (Fewer than two dwords of scales in all: the only one, and the loads, made
+  // without a branch in the pipeline, read the weight's scales and are dropped.)
+  const bool as_tiny = as_last < 4;
+  uint32_t as_only = 0;
+  if constexpr (!kPackedA)
+    if (as_tiny) as_only = *reinterpret_cast<const uint32_t*>(as_base);
+  const uint8_t* const as_src = as_tiny ? Wps : as_base;
+  const uint32_t as_most = as_tiny ? 0u : as_last - 4;
+  uint32_t as_at[kSc];     // byte offset of the entry's row from as_base, plus 4 its step
+  struct Pairs {
+    uint2 v[kSc];
+  };
+  int part_steps[2];       // steps whose part 2h + l / 32 lies inside K_aug
+  if constexpr (!kPackedA) {
+#pragma unroll
+    for (int i = 0; i < kSc; ++i)
+      as_at[i] = as_lead + 4 * (tid & 3) +
+                 static_cast<uint32_t>(min(row_begin + ((tid + i * kThreads) >> 2), row_end - 1)) * nb;
+    part_steps[0] = (nb - (lane >> 5) + 3) >> 2;
+    part_steps[1] = (nb - (lane >> 5) + 1) >> 2;
+  }
+  auto fetch_scales = [&](int s, Pairs& o) {
+#pragma unroll
+    for (int i = 0; i < kSc; ++i) {
+      const uint32_t at = (as_at[i] + 4 * s) & ~3u;
+      struct __attribute__((aligned(4))) Dwords { uint32_t d[2]; };
+      const Dwords v = *reinterpret_cast<const Dwords*>(as_src + min(at, as_most));
+      o.v[i] = make_uint2(v.d[0], v.d[1]);
+    }
+  };
+  auto place_scales = [&](int s, const Pairs& o, int w) {   // w: the window's place in aw_lds
+#pragma unroll
+    for (int i = 0; i < kSc; ++i) {
+      const uint32_t at = as_at[i] + 4 * s;
+      const uint32_t second = as_tiny ? as_only : o.v[i].y;
+      const uint32_t first = (at & ~3u) >= as_last ? second : o.v[i].x;
+      *reinterpret_cast<uint32_t*>(aw_lds + w + ((tid & 3) * kBM + ((tid + i * kThreads) >> 2)) * 4) =
+          __builtin_amdgcn_alignbyte(second, first, at & 3u);
+    }
+  };
+  const uint32_t aw_lb = (wm * kTM + (lane & 31)) * 4;
+  auto read = [&](const uint8_t* st, auto hc, Half& o, int aw) {   // aw: the step's A scales in aw_lds (row-major)
     constexpr int h = decltype(hc)::value;
 #pragma unroll
     for (int i = 0; i < kFM; ++i) {
-      o.a[i] = *reinterpret_cast<const uint4*>(st + a_lb + (2 * i * 1024 + h * 512));
-      o.sa[i] = *reinterpret_cast<const uint32_t*>(
-          st + as_lb + (kScaleDword ? 32 * i * 4 : 2 * i * 256 + h * 128));
+      o.a[i] = *reinterpret_cast<const uint4*>(
+          st + (kPackedA || h == 0 ? a_lb : a_lb1) + (2 * i * 1024 + (kPackedA ? h * 512 : 0)));
+      if constexpr (kPackedA)
+        o.sa[i] = *reinterpret_cast<const uint32_t*>(st + as_lb + (2 * i * 256 + h * 128));
+      else
+        o.sa[i] = *reinterpret_cast<const uint32_t*>(aw_lds + aw + aw_lb + 32 * i * 4);
     }
 #pragma unroll
     for (int j = 0; j < kFN; ++j) {
@@ -440,11 +485,13 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
     for (int j = 0; j < kFN; ++j) sb[j] = o.sb[j] >> qshift;
 #pragma unroll
     for (int i = 0; i < kFM; ++i) {
-      const uint32_t sa = kScaleDword ? (o.sa[i] >> a_shift) : (kPackedA ? (o.sa[i] >> qshift) : o.sa[i]);
+      uint32_t sa;
+      if constexpr (kPackedA) sa = o.sa[i] >> qshift;
+      else sa = s < part_steps[h] ? o.sa[i] >> (8 * (lane >> 5)) : 0x7F7F7F7Fu;   // past K_aug: 1.0 (the weight is 0)
 #pragma unroll
       for (int j = 0; j < kFN; ++j)
-        acc[i][j] = dev::mfma_fp4_32x32x64_sel<kScaleDword ? 2 * h : 0, 0>(o.a[i], o.b[j], sa,
-                                                                          sb[j], acc[i][j]);
+        acc[i][j] = dev::mfma_fp4_32x32x64_sel<kPackedA ? 0 : 2 * h, 0>(o.a[i], o.b[j], sa, sb[j],
+                                                                        acc[i][j]);
     }
   };
 
@@ -462,21 +509,32 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
   // read has landed (a wait count chosen at run time leaves it a path on which
   // it drains every load first).  Scheduling barriers keep each wait and
   // barrier between the MFMAs it separates.
+  Pairs first_pairs, pairs;   // both before the loads: the loop then never waits for what follows them
+  if constexpr (!kPackedA) {
+    fetch_scales(s_lo, first_pairs);
+    fetch_scales(min(s_lo + kU, s_hi - 1), pairs);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   static_for<kNS>([&](auto pc) {
     issue(min(s_lo + static_cast<int>(decltype(pc)::value), s_hi - 1), stage(pc));
   });
   wait_vmcnt<(kNS - 1) * kLoads>();
+  if constexpr (!kPackedA) {
+    __builtin_amdgcn_sched_barrier(0);
+    place_scales(s_lo, first_pairs, 0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the window is written
+  }
   __builtin_amdgcn_s_barrier();
   Half h0, h1;
-  read(st0, IntC<0>{}, h0);
-  auto body = [&](int s0, auto pc, auto gc) {
+  read(st0, IntC<0>{}, h0, 0);
+  auto body = [&](int s0, auto pc, auto gc, int aw, int aw_next) {
     constexpr int p = decltype(pc)::value;
     constexpr bool kGuard = decltype(gc)::value;
     const int s = s0 + p;
     const bool live = !kGuard || s < s_hi;
     __builtin_amdgcn_sched_barrier(0);
     if (live) mfma(h0, IntC<0>{}, s);
-    read(stage(pc), IntC<1>{}, h1);
+    read(stage(pc), IntC<1>{}, h1, aw + p * kBM * 4);
     if constexpr (!kGuard) interleave<kMfmas / 2, 0, kReads / 2>();
     __builtin_amdgcn_sched_barrier(0);
     wait_vmcnt<(kNS - 2) * kLoads>();
@@ -484,16 +542,34 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
     __builtin_amdgcn_sched_barrier(0);
     issue(min(s + kNS, s_hi - 1), stage(pc));
     if (live) mfma(h1, IntC<1>{}, s);
-    read(stage(IntC<p + 1>{}), IntC<0>{}, h0);
+    read(stage(IntC<p + 1>{}), IntC<0>{}, h0, p + 1 < kU ? aw + (p + 1) * kBM * 4 : aw_next);
     if constexpr (!kGuard) interleave<kMfmas / 2, kLoads, kReads / 2>();
     __builtin_amdgcn_sched_barrier(0);
   };
   // Whole groups of kU steps without guards (so the scheduler can interleave
   // the LDS reads with the MFMAs), then one guarded group for the rest.
+  // Row-major: each group first puts the next group's scale window into the
+  // window buffer that the group before it has finished with (its last reads lie
+  // before that group's last barrier), and loads the one after (of steps at most
+  // s_hi - 1: valid rows).
+  int aw = 0, aw_next = kWindow;   // offsets, not pointers: the reads are then known to be of aw_lds
+  auto window = [&](int s0) {
+    if constexpr (!kPackedA) {
+      place_scales(min(s0 + kU, s_hi - 1), pairs, aw_next);
+      fetch_scales(min(s0 + 2 * kU, s_hi - 1), pairs);
+    }
+  };
   int s0 = s_lo;
-  for (; s0 + kU <= s_hi; s0 += kU)
-    static_for<kU>([&](auto pc) { body(s0, pc, IntC<0>{}); });
-  if (s0 < s_hi) static_for<kU>([&](auto pc) { body(s0, pc, IntC<1>{}); });
+  for (; s0 + kU <= s_hi; s0 += kU) {
+    window(s0);
+    static_for<kU>([&](auto pc) { body(s0, pc, IntC<0>{}, aw, aw_next); });
+    aw ^= kWindow;
+    aw_next ^= kWindow;
+  }
+  if (s0 < s_hi) {
+    window(s0);
+    static_for<kU>([&](auto pc) { body(s0, pc, IntC<1>{}, aw, aw_next); });
+  }
   wait_vmcnt<0>();   // no direct-to-LDS write outlives the workgroup
 
   // Element q of a lane's fragment is C[8 (q / 4) + 4 (l / 32) + q % 4][l % 32]:
@@ -857,21 +933,15 @@ hipError_t launch_shape_scales(const uint8_t* Aq, const uint8_t* Asc, int M, con
   return hipGetLastError();
 }
 
-// Activation scale rows are dword-aligned when K_aug is a multiple of 128
-// (K_aug / 32 scale bytes per row) and Asc is; otherwise they are staged a
-// byte at a time.
-template <int kBM, int kBN, int kWM, int kWN, int kNSDword, int kNSByte>
+template <int kBM, int kBN, int kWM, int kWN, int kNS>
 hipError_t launch_shape(const uint8_t* Aq, const uint8_t* Asc, int M, const int32_t* off, int E,
                         const uint8_t* Wp, const uint8_t* Wps, int N, int K_aug, float* Y,
                         bool packed, int tile_base, int region_tiles, int splits, float* ws,
                         hipStream_t stream) {
   if (packed)
-    return launch_shape_scales<kBM, kBN, kWM, kWN, kNSDword, kAPacked>(
+    return launch_shape_scales<kBM, kBN, kWM, kWN, kNS, kAPacked>(
         Aq, Asc, M, off, E, Wp, Wps, N, K_aug, Y, tile_base, region_tiles, splits, ws, stream);
-  if (K_aug % 128 == 0 && (reinterpret_cast<uintptr_t>(Asc) & 3u) == 0)
-    return launch_shape_scales<kBM, kBN, kWM, kWN, kNSDword, kARowDword>(
-        Aq, Asc, M, off, E, Wp, Wps, N, K_aug, Y, tile_base, region_tiles, splits, ws, stream);
-  return launch_shape_scales<kBM, kBN, kWM, kWN, kNSByte, kARowByte>(
+  return launch_shape_scales<kBM, kBN, kWM, kWN, kNS, kARow>(
       Aq, Asc, M, off, E, Wp, Wps, N, K_aug, Y, tile_base, region_tiles, splits, ws, stream);
 }
 
@@ -883,38 +953,47 @@ hipError_t launch_region(const uint8_t* Aq, const uint8_t* Asc, int M, const int
                          int shape, bool packed, int tile_base, int region_tiles,
                          hipStream_t stream, int splits = 1, float* ws = nullptr) {
   switch (shape) {
-    case 0: return launch_shape<256, 256, 2, 4, 4, 3>(Aq, Asc, M, off, E, Wp, Wps, N, K_aug, Y, packed, tile_base, region_tiles, splits, ws, stream);
-    case 1: return launch_shape<256, 128, 2, 2, 4, 4>(Aq, Asc, M, off, E, Wp, Wps, N, K_aug, Y, packed, tile_base, region_tiles, splits, ws, stream);
-    case 3: return launch_shape<256, 320, 4, 2, 3, 3>(Aq, Asc, M, off, E, Wp, Wps, N, K_aug, Y, packed, tile_base, region_tiles, splits, ws, stream);
-    default: return launch_shape<128, 128, 2, 2, 4, 4>(Aq, Asc, M, off, E, Wp, Wps, N, K_aug, Y, packed, tile_base, region_tiles, splits, ws, stream);
+    case 0: return launch_shape<256, 256, 2, 4, 4>(Aq, Asc, M, off, E, Wp, Wps, N, K_aug, Y, packed, tile_base, region_tiles, splits, ws, stream);
+    case 1: return launch_shape<256, 128, 2, 2, 4>(Aq, Asc, M, off, E, Wp, Wps, N, K_aug, Y, packed, tile_base, region_tiles, splits, ws, stream);
+    case 3: return launch_shape<256, 320, 4, 2, 3>(Aq, Asc, M, off, E, Wp, Wps, N, K_aug, Y, packed, tile_base, region_tiles, splits, ws, stream);
+    default: return launch_shape<128, 128, 2, 2, 4>(Aq, Asc, M, off, E, Wp, Wps, N, K_aug, Y, packed, tile_base, region_tiles, splits, ws, stream);
   }
 }
 
 struct Shape {
   int id, bm, bn;
-  double eff_rows;      // measured throughput per tile area relative to 256 x 256 (row-major A)
-  // Packed A, by the most tiles any CU runs (1, 2, 3 or more), relative to one
-  // 256 x 256 tile per CU; fitted to the down_proj sweep (M = 1024 .. 8192, N =
-  // 2560, K + k = 9984, weights rotated): 128 x 128 workgroups fit two to a CU
-  // and hide each other's latency, so two per CU run far better than one.
+  // Throughput per tile area by the most tiles any CU runs (1, 2, 3 or more),
+  // relative to one 256 x 256 tile of a packed A per CU.  Packed: fitted to the
+  // down_proj sweep (M = 1024 .. 8192, N = 2560, K + k = 9984, weights rotated):
+  // 128 x 128 workgroups fit two to a CU and hide each other's latency, so two per
+  // CU run far better than one.  Row-major: the packed factors over the measured
+  // ratio of the two layouts (half-line code loads): 1.18, 1.27, 1.26, 1.10.
   double eff_packed[3];
+  double eff_rows[3];
+  // Row-major calls decide whether to split along K by these, whatever the loads:
+  // the workspace that a call needs (and prq_gemm_noalloc's limit on it) stays
+  // what callers have sized theirs for.
+  double eff_rows_split;
 };
+enum Efficiency { kEffPacked, kEffRows, kEffRowsSplit };
 // 256 x 320 (8 waves, 64 x 160 each, 3 stages): where it fills the CUs evenly
 // it beats every other plan -- 8192 x 2560 x 9984 in one round of 256 tiles,
 // 106 against 120 us for 256 x 256 over 2048 columns and 128 x 128 over the
 // rest; 4096 x 9728 x 2624, 80 against 93 us -- and loses elsewhere (half-empty
 // rounds); its factors are set to pick it exactly there.
-constexpr Shape kShapes[] = {{0, 256, 256, 1.0, {1.0, 0.92, 0.92}},
-                             {1, 256, 128, 0.63, {0.73, 0.87, 0.80}},
-                             {2, 128, 128, 0.5, {0.58, 0.81, 0.68}},
-                             {3, 256, 320, 0.5, {0.9, 0.9, 0.85}}};
+constexpr Shape kShapes[] = {{0, 256, 256, {1.0, 0.92, 0.92}, {0.85, 0.78, 0.78}, 1.0},
+                             {1, 256, 128, {0.73, 0.87, 0.80}, {0.58, 0.69, 0.63}, 0.63},
+                             {2, 128, 128, {0.58, 0.81, 0.68}, {0.46, 0.64, 0.54}, 0.5},
+                             {3, 256, 320, {0.9, 0.9, 0.85}, {0.82, 0.82, 0.77}, 0.5}};
 
 // Cost of `tiles` tiles of shape s on `cus` CUs in tile-area units (one
 // 256 x 256 tile alone on its CU = 65536): the busiest CU's tiles over the
 // shape's efficiency at that load.
-double shape_cost(const Shape& s, bool packed, long tiles, int cus) {
+double shape_cost(const Shape& s, Efficiency which, long tiles, int cus) {
   const long per_cu = (tiles + cus - 1) / cus;
-  const double eff = packed ? s.eff_packed[std::min<long>(per_cu, 3) - 1] : s.eff_rows;
+  const double eff = which == kEffRowsSplit
+                         ? s.eff_rows_split
+                         : (which == kEffPacked ? s.eff_packed : s.eff_rows)[std::min<long>(per_cu, 3) - 1];
   return per_cu * static_cast<double>(s.bm) * s.bn / eff;
 }
 
@@ -938,7 +1017,7 @@ constexpr double kFillSteps = 3.0;      // pipeline fill, drain and Y store, in 
 constexpr double kLaunchUs = 3.0;       // a second launch
 constexpr double kReduceBytesPerUs = 5.0e6;
 
-TilePlan plan_tile_gemm(int M, int N, int K_aug, int num_cus, bool packed, bool allow_split) {
+TilePlan plan_tile_gemm_by(int M, int N, int K_aug, int num_cus, Efficiency which, bool allow_split) {
   const int cus = std::max(num_cus, 1);
   const int ntiles = N / 16;
   const int steps = (K_aug + kStepK - 1) / kStepK;
@@ -948,7 +1027,7 @@ TilePlan plan_tile_gemm(int M, int N, int K_aug, int num_cus, bool packed, bool 
     const int per = (steps + splits - 1) / splits;
     const long wgs = tiles * ((steps + per - 1) / per);
     // per-step time of the busiest CU: kStepUs256 per 256 x 256 tile alone
-    const double step_us = kStepUs256 * shape_cost(s, packed, wgs, cus) / 65536.0;
+    const double step_us = kStepUs256 * shape_cost(s, which, wgs, cus) / 65536.0;
     double c = (per + kFillSteps) * step_us;
     if (splits > 1)   // partials written, then Y and the partials read and Y written
       c += kLaunchUs + 2.0 * ((steps + per - 1) / per) * 4.0 * M * N / kReduceBytesPerUs;
@@ -990,6 +1069,15 @@ TilePlan plan_tile_gemm(int M, int N, int K_aug, int num_cus, bool packed, bool 
   return best;
 }
 
+TilePlan plan_tile_gemm(int M, int N, int K_aug, int num_cus, bool packed, bool allow_split) {
+  if (packed) return plan_tile_gemm_by(M, N, K_aug, num_cus, kEffPacked, allow_split);
+  if (allow_split) {
+    const TilePlan split = plan_tile_gemm_by(M, N, K_aug, num_cus, kEffRowsSplit, true);
+    if (split.splits > 1) return split;
+  }
+  return plan_tile_gemm_by(M, N, K_aug, num_cus, kEffRows, false);
+}
+
 hipError_t launch_plan(const uint8_t* Aq, const uint8_t* Asc, int M, const uint8_t* Wp,
                        const uint8_t* Wps, int N, int K_aug, float* Y, bool packed,
                        const TilePlan& plan, float* ws, hipStream_t stream) {
@@ -1005,21 +1093,6 @@ hipError_t launch_plan(const uint8_t* Aq, const uint8_t* Asc, int M, const uint8
 }
 
 }  // namespace
-
-int choose_tile_shape(int M_rows, int N, int num_cus, bool packed) {
-  // One shape over all columns (grouped calls and the tuning entry).
-  int best = 2;
-  double best_cost = 1e300;
-  for (const Shape& s : kShapes) {
-    const long tiles = static_cast<long>((M_rows + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn);
-    const double c = shape_cost(s, packed, tiles, std::max(num_cus, 1));
-    if (c < best_cost) {
-      best_cost = c;
-      best = s.id;
-    }
-  }
-  return best;
-}
 
 hipError_t launch_gemm_tile(const uint8_t* Aq, const uint8_t* Asc, int M,
                             const int32_t* group_offsets, int E, const uint8_t* Wp,

@@ -405,3 +405,79 @@ def test_pack_weight_layout(E, N, K_aug):
     ref_p, ref_s = _pack_reference(Wq, Wsc)
     np.testing.assert_array_equal(host(W.Wp), ref_p)
     np.testing.assert_array_equal(host(W.Wps), ref_s)
+
+
+def _at_byte(a, offset):
+    """`a` on the device starting `offset` bytes past a 256-byte boundary, with
+    scale bytes of 255 (NaN) right before and after it."""
+    buf = torch.full((a.size + 512,), 255, dtype=torch.uint8, device="cuda")
+    view = buf[256 + offset:256 + offset + a.size].view(a.shape)
+    view.copy_(dev(a))
+    return view
+
+
+# (M, N, K_aug, offset of Asc): fewer scale bytes than two dwords; rows of one to
+# five steps (windows shorter than four steps, windows cut by the last row) at
+# every scale alignment; a whole number of steps (aligned and not); more steps
+# than a window with a remainder; split along K.
+ROW_SCALES = [(1, 16, 32, 0), (2, 16, 32, 3), (3, 32, 96, 1), (65, 48, 160, 0), (66, 48, 160, 1),
+              (67, 48, 416, 2), (68, 48, 544, 3), (129, 160, 640, 0), (129, 160, 640, 1),
+              (257, 336, 1184, 3), (300, 512, 2592, 2), (300, 512, 9984, 0), (333, 256, 4192, 1)]
+
+
+@pytest.mark.parametrize("M,N,K_aug,offset", ROW_SCALES)
+def test_tile_row_major_scales_at_any_alignment(M, N, K_aug, offset):
+    """Row-major activation scales read as aligned dwords around rows of any
+    alignment: the bytes of neighbouring rows (here rows of NaN scales between
+    ordinary ones) and past the array must not reach a row's result.  Planned
+    tile call, and every tile shape forced."""
+    import ctypes
+    from paper_2609_22106_amd import build
+    prq = _prq()
+    rng = np.random.default_rng(M + N + K_aug + offset)
+    Aq, Asc = inputs.random_mxfp4(rng, M, K_aug)
+    Wq, Wsc = inputs.random_mxfp4(rng, N, K_aug)
+    ref = pq.gemm(Aq, Asc, Wq, Wsc)
+    bad = np.zeros(M, bool)
+    bad[1::3] = True                     # rows whose scales are all NaN
+    Asc = Asc.copy()
+    Asc[bad] = 255
+    W = _packed(Wq, Wsc)
+    A, As = dev(Aq), _at_byte(Asc, offset)
+    say("row-major scales case:", M, N, K_aug, offset)
+
+    def check(Y, what):
+        torch.cuda.synchronize()
+        y = host(Y)
+        assert np.isnan(y[bad]).all(), what
+        assert_gemm_close(y[~bad], ref[~bad], what)
+
+    check(prq.prq_gemm(A, As, W, Y=nan_output(M, N), variant=prq.GEMM_TILE), "planned")
+    lib = ctypes.CDLL(build.PROBE_LIB)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())  # noqa: E731
+    for shape in range(4):
+        Y = nan_output(M, N)
+        st = lib.prq_tune_gemm_tile(p(A), p(As), M, None, 1, p(W.Wp), p(W.Wps), N, K_aug, p(Y), shape,
+                                    ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert st == 0
+        check(Y, f"shape {shape}")
+
+
+def test_grouped_row_major_scales_at_odd_alignment():
+    """Grouped row-major tiles: experts' first rows at every scale alignment."""
+    prq = _prq()
+    rng = np.random.default_rng(9)
+    counts, N, K_aug = [70, 0, 129, 1, 258, 65], 48, 544
+    off = inputs.routed_offsets(counts)
+    M = int(off[-1])
+    Aq, Asc = inputs.random_mxfp4(rng, M, K_aug)
+    Wq, Wsc = inputs.random_mxfp4(rng, (len(counts), N), K_aug)
+    Y = nan_output(M, N)
+    say("grouped row-major scales case")
+    prq.prq_grouped_gemm(dev(Aq), _at_byte(Asc, 3), dev(off), _packed(Wq, Wsc), Y=Y, variant=prq.GEMM_TILE)
+    torch.cuda.synchronize()
+    y = host(Y)
+    for e in range(len(counts)):
+        r0, r1 = off[e], off[e + 1]
+        if r1 > r0:
+            assert_gemm_close(y[r0:r1], pq.gemm(Aq[r0:r1], Asc[r0:r1], Wq[e], Wsc[e]), f"expert {e}")

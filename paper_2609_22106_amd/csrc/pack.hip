@@ -23,47 +23,49 @@ namespace {
 
 constexpr int kPackThreads = 256;
 
-// One thread per (e, t, s, lane): copies 16 bytes (4 dwords of one row).
-__global__ __launch_bounds__(kPackThreads) void pack_codes_kernel(
-    const uint8_t* __restrict__ Wq, int N, int K_aug, int E, uint8_t* __restrict__ Wp) {
+// One launch for both (128 experts of 2048 x 832, 232 MB: two launches 52.2 us, one
+// 49.0, 4.7 TB/s where a plain copy reaches 5.1):
+// workgroups [0, scale_blocks) gather scales -- first, so that their short loads
+// run beside the code copies -- the rest copy codes.
+//
+// Codes: one thread per (e, t, s, lane), 16 bytes (4 dwords of one row).  Scales:
+// one thread per (e, t, q, lane), 4 scale bytes into a dword.  Index: the type
+// that block numbers are divided in.
+template <class Index>
+__global__ __launch_bounds__(kPackThreads) void pack_weight_kernel(
+    const uint8_t* __restrict__ Wq, const uint8_t* __restrict__ Wsc, int N, int K_aug, int E,
+    uint8_t* __restrict__ Wp, uint32_t* __restrict__ Wps, uint32_t scale_blocks) {
   const int S = (K_aug + 127) / 128;
   const int T = N / 16;
-  const int64_t total = static_cast<int64_t>(E) * T * S * 64;
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * kPackThreads + threadIdx.x;
-  if (i >= total) return;
-  const int l = static_cast<int>(i & 63);
-  const int64_t blk = i >> 6;                 // (e * T + t) * S + s
-  const int s = static_cast<int>(blk % S);
-  const int64_t et = blk / S;                 // e * T + t
-  const int64_t row = et * 16 + (l & 15);     // row within [E * N]
+  const int l = static_cast<int>(threadIdx.x) & 63;
+  if (blockIdx.x < scale_blocks) {
+    const int Q = (S + 3) / 4;
+    const int nb = K_aug / 32;
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * kPackThreads + threadIdx.x;
+    if (i >= static_cast<int64_t>(E) * T * Q * 64) return;
+    const Index grp = static_cast<Index>(i >> 6);        // (e * T + t) * Q + q
+    const int q = static_cast<int>(grp % static_cast<Index>(Q));
+    const uint8_t* const row = Wsc + (static_cast<int64_t>(grp / static_cast<Index>(Q)) * 16 + (l & 15)) * nb;
+    uint32_t d = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int b = 4 * (4 * q + j) + (l >> 4);
+      const uint32_t sc = b < nb ? row[b] : 127u;
+      d |= sc << (8 * j);
+    }
+    Wps[i] = d;
+    return;
+  }
+  const int64_t i = static_cast<int64_t>(blockIdx.x - scale_blocks) * kPackThreads + threadIdx.x;
+  if (i >= static_cast<int64_t>(E) * T * S * 64) return;
+  const Index blk = static_cast<Index>(i >> 6);          // (e * T + t) * S + s
+  const int s = static_cast<int>(blk % static_cast<Index>(S));
+  const int64_t row = static_cast<int64_t>(blk / static_cast<Index>(S)) * 16 + (l & 15);   // within [E * N]
   const int kel = s * 128 + (l >> 4) * 32;
   uint4 v = make_uint4(0, 0, 0, 0);
   if (kel < K_aug)
     v = *reinterpret_cast<const uint4*>(Wq + row * (K_aug / 2) + kel / 2);
   *reinterpret_cast<uint4*>(Wp + i * 16) = v;
-}
-
-// One thread per (e, t, q, lane): gathers 4 scale bytes into a dword.
-__global__ __launch_bounds__(kPackThreads) void pack_scales_kernel(
-    const uint8_t* __restrict__ Wsc, int N, int K_aug, int E, uint32_t* __restrict__ Wps) {
-  const int S = (K_aug + 127) / 128;
-  const int Q = (S + 3) / 4;
-  const int T = N / 16;
-  const int nb = K_aug / 32;
-  const int64_t total = static_cast<int64_t>(E) * T * Q * 64;
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * kPackThreads + threadIdx.x;
-  if (i >= total) return;
-  const int l = static_cast<int>(i & 63);
-  const int64_t grp = i >> 6;                 // (e * T + t) * Q + q
-  const int q = static_cast<int>(grp % Q);
-  const int64_t row = (grp / Q) * 16 + (l & 15);
-  uint32_t d = 0;
-  for (int j = 0; j < 4; ++j) {
-    const int b = 4 * (4 * q + j) + (l >> 4);
-    const uint32_t sc = b < nb ? Wsc[row * nb + b] : 127u;
-    d |= sc << (8 * j);
-  }
-  Wps[i] = d;
 }
 
 }  // namespace
@@ -80,10 +82,16 @@ hipError_t launch_pack_weight(const uint8_t* Wq, const uint8_t* Wsc, int N, int 
                               uint8_t* Wp, uint8_t* Wps, hipStream_t stream) {
   const int64_t nc = static_cast<int64_t>(packed_code_bytes(N, K_aug, E) / 16);
   const int64_t ns = static_cast<int64_t>(packed_scale_bytes(N, K_aug, E) / 4);
-  pack_codes_kernel<<<static_cast<unsigned>((nc + kPackThreads - 1) / kPackThreads), kPackThreads, 0,
-                      stream>>>(Wq, N, K_aug, E, Wp);
-  pack_scales_kernel<<<static_cast<unsigned>((ns + kPackThreads - 1) / kPackThreads), kPackThreads, 0,
-                       stream>>>(Wsc, N, K_aug, E, reinterpret_cast<uint32_t*>(Wps));
+  const int64_t code_blocks = (nc + kPackThreads - 1) / kPackThreads;
+  const int64_t scale_blocks = (ns + kPackThreads - 1) / kPackThreads;
+  const dim3 grid(static_cast<unsigned>(code_blocks + scale_blocks));
+  uint32_t* const ps = reinterpret_cast<uint32_t*>(Wps);
+  if (nc / 64 < (int64_t{1} << 32))   // 32-bit divisions of the block numbers
+    pack_weight_kernel<uint32_t><<<grid, kPackThreads, 0, stream>>>(Wq, Wsc, N, K_aug, E, Wp, ps,
+                                                                    static_cast<uint32_t>(scale_blocks));
+  else
+    pack_weight_kernel<uint64_t><<<grid, kPackThreads, 0, stream>>>(Wq, Wsc, N, K_aug, E, Wp, ps,
+                                                                    static_cast<uint32_t>(scale_blocks));
   return hipGetLastError();
 }
 

@@ -257,7 +257,8 @@ __global__ __launch_bounds__(kRowsThreads) void act_quant_rows_kernel(
   const int rot = (threadIdx.x >> 3) & 3;
   const int rs = (4 - rot) & 3;
   PackedUnit un;
-  int cur_g = kGrouped ? dev::find_group(offsets, G, r0) : 0;
+  dev::GroupCursor gc(kGrouped ? dev::wave_find_group(offsets, G, r0) : 0);
+  int cur_g = gc.g;
   load_packed_unit(perm, inv, cur_g, K, uc, &un, rot);
   __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8));   // vmcnt(0): copies and entries
   __syncthreads();
@@ -266,7 +267,7 @@ __global__ __launch_bounds__(kRowsThreads) void act_quant_rows_kernel(
   for (int rr = 0; rr < n; ++rr) {
     const int r = r0 + rr;
     if (kGrouped) {
-      const int g = dev::find_group(offsets, G, r);
+      const int g = gc.at(offsets, G, r);
       if (g != cur_g) {
         load_packed_unit(perm, inv, g, K, uc, &un, rot);
         cur_g = g;
@@ -372,7 +373,7 @@ __global__ __launch_bounds__(kLdsThreads) void act_quant_lds_kernel(
   const int rs = (4 - rot) & 3;
   PackedUnit un[kUnits];
   int cur_g = -1;
-  dev::GroupCursor gc;   // this thread's rows only increase
+  dev::GroupCursor gc(kGrouped && r0 < M ? dev::wave_find_group(offsets, G, r0) : 0);   // rows only increase
   int pass = 0;
   for (int rb = r0; rb < r1; rb += rpp, ++pass) {
     uint4* const sb = (pass & 1) ? buf1 : buf0;
@@ -417,15 +418,14 @@ __global__ __launch_bounds__(kLdsThreads) void act_quant_lds_kernel(
       }
     }
   }
-  // Packed layout: the workgroup with the last row also fills the rows of the
-  // last 16-row block past M (zero codes, scale byte 127).
+  // Packed layout: the rows of the last 16-row block past M (zero codes, scale
+  // byte 127), one to a workgroup (all of them in the workgroup with the last rows
+  // kept it 2 us longer: 65 x 2560 5.6 us, 64 x 2560 2.8).
   if constexpr (kPacked) {
-    if (r0 < r1 && r1 == M) {
-      for (int r = M; r < ((M + 15) & ~15); ++r) {
-        const PackedSink psink(Aq, Asc, r, steps, sgroups);
-        for (int v = tid; v < steps * 16; v += kLdsThreads) psink.word(v, 0u);
-        for (int b = tid; b < sgroups * 16; b += kLdsThreads) psink.scale(b, 127u);
-      }
+    for (int r = M + static_cast<int>(blockIdx.x); r < ((M + 15) & ~15); r += static_cast<int>(gridDim.x)) {
+      const PackedSink psink(Aq, Asc, r, steps, sgroups);
+      for (int v = tid; v < steps * 16; v += kLdsThreads) psink.word(v, 0u);
+      for (int b = tid; b < sgroups * 16; b += kLdsThreads) psink.scale(b, 127u);
     }
   }
 }
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(kDmaThreads) void act_quant_dma_kernel(
     __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8));   // vmcnt(0)
     cur_g = g;
   };
-  dev::GroupCursor gc;
+  dev::GroupCursor gc(kGrouped ? dev::wave_find_group(offsets, G, r0) : 0);
   if (!copier) load_units(kGrouped ? gc.at(offsets, G, r0) : 0);
 
   // Rows [lo, hi) of the window of rows [w0, w0 + 8) from LDS to the packed
@@ -621,11 +621,11 @@ __global__ __launch_bounds__(kDmaThreads) void act_quant_dma_kernel(
     if (!copier) flush(w0, max(r0, w0), r1);
   }
 
-  // Packed layout: the workgroup with the last row also fills the rows of the
-  // last 16-row block past M (zero codes, scale byte 127).
+  // Packed layout: the rows of the last 16-row block past M, one to a workgroup
+  // (as in act_quant_lds_kernel).
   if constexpr (kPacked) {
-    if (r1 == M && !copier) {
-      for (int r = M; r < ((M + 15) & ~15); ++r) {
+    if (!copier) {
+      for (int r = M + static_cast<int>(blockIdx.x); r < ((M + 15) & ~15); r += static_cast<int>(gridDim.x)) {
         const PackedSink psink(Aq, Asc, r, steps, sgroups);
         for (int v = tid; v < steps * 16; v += kComputeThreads) psink.word(v, 0u);
         for (int b = tid; b < sgroups * 16; b += kComputeThreads) psink.scale(b, 127u);
@@ -738,6 +738,16 @@ void set_rows_lds_limit() {
   });
 }
 
+// Whether the few-rows kernel takes a call (row-major, packed): up to 64 rows, and
+// as long as its copies of a row (a whole one for every 256 units) stay few.
+// us, few-rows / many-rows kernel, row-major: 65 x 9728 3.7 / 4.6, 256 x 2560 3.1 /
+// 3.1, 512 x 768 in 128 groups 3.1 / 3.9, 1024 x 768 3.0 / 3.2; packed: 65 x 9728
+// 4.0 / 5.5, 256 x 2560 3.4 / 3.6, 256 x 4096 3.7 / 3.7, 256 x 9728 7.2 / 6.4, 512 x
+// 768 in groups 3.5 / 4.4, 1024 x 768 3.5 / 3.6, 2048 x 768 4.7 / 4.2.
+bool few_rows(int M, int K) {
+  return M <= 64 || (M <= 1024 && static_cast<int64_t>(M) * K <= 1024 * 768);
+}
+
 // Few rows into the packed layout: one row per workgroup row, and workgroup
 // rows up to the end of the last 16-row block that write its padding rows.
 hipError_t launch_rows_packed(const uint16_t* X, int64_t ld_x, int M, int K, int k_tail,
@@ -764,7 +774,7 @@ hipError_t launch_act_quant_kernel(const uint16_t* X, int64_t ld_x, int M, int K
                                    int num_cus, int kernel, hipStream_t stream) {
   const bool grouped = group_offsets && G > 1;
   const int units = K >> 3;
-  if (kernel == 1 || (kernel == 0 && M <= 64)) {
+  if (kernel == 1 || (kernel == 0 && few_rows(M, K))) {
     // Few rows: spread the positions over workgroups, one row per workgroup
     // row up to 64 rows (measured on the 9728 -> 9984 down_proj row against 16
     // row chunks: M = 32 3.36 -> 2.77 us, M = 64 4.67 -> 3.22 warm, 3.90 -> 3.24
@@ -772,7 +782,7 @@ hipError_t launch_act_quant_kernel(const uint16_t* X, int64_t ld_x, int M, int K
     // (forced for more rows) at most ~16 row chunks; a workgroup's rows are
     // staged whole in LDS (at most 4 rows of 32 KiB).
     const int pitch = (2 * K + 1023) / 1024 * 1024;
-    const int rows_per_wg = M <= 64 ? 1 : std::max(1, std::min((M + 15) / 16, 4 * 32768 / pitch));
+    const int rows_per_wg = few_rows(M, K) ? 1 : std::max(1, std::min((M + 15) / 16, 4 * 32768 / pitch));
     const dim3 grid((units + kRowsThreads - 1) / kRowsThreads, (M + rows_per_wg - 1) / rows_per_wg);
     const size_t lds = static_cast<size_t>(std::min(rows_per_wg, M)) * pitch;
     if (grouped) {
@@ -841,7 +851,7 @@ hipError_t launch_act_quant_packed_kernel(const uint16_t* X, int64_t ld_x, int M
   // Few rows (decode): the few-rows kernel, as for the row-major output (the
   // whole-K decode GEMM then copies each 16-row group's operand in whole
   // kilobytes).
-  if (kernel == 1 || (kernel == 0 && M <= 64))
+  if (kernel == 1 || (kernel == 0 && few_rows(M, K)))
     return launch_rows_packed(X, ld_x, M, K, k_tail, inv_scale_pos, perm, off, G, Ap, Aps, stream);
   if (kernel == 3 || kernel == 4 || (kernel == 0 && K >= 2048)) {
     const int window = kernel == 3 ? 1 : kernel == 4 ? 2 : 0;

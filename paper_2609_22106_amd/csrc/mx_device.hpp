@@ -137,28 +137,32 @@ __device__ __forceinline__ v16f mfma_fp4_32x32x64_sel(const uint4& a, const uint
 }
 
 // Group g with off[g] <= row < off[g+1] for non-decreasing offsets
-// (empty groups are skipped): the largest g in [0, G) with off[g] <= row.
-__device__ __forceinline__ int find_group(const int32_t* __restrict__ off, int G, int row) {
-  int lo = 0, hi = G - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (off[mid] <= row)
-      lo = mid;
-    else
-      hi = mid - 1;
+// (empty groups are skipped): the largest g in [0, G) with off[g] <= row.  A
+// whole wave looks for one row (every lane active): it counts the offsets at
+// or below the row, 64 to a load, all loads independent.  A binary search waits
+// for 7 loads one after the other at 128 groups: 512 rows of 768 in 128 groups
+// took 3.9 us with it, 3.4 without (many-rows quantizer, row-major).
+__device__ __forceinline__ int wave_find_group(const int32_t* __restrict__ off, int G, int row) {
+  const int lane = static_cast<int>(threadIdx.x) & 63;
+  int n = 0;
+#pragma unroll 4
+  for (int b = 0; b < G; b += 64) {
+    const int i = b + lane;
+    const int at = off[i < G ? i : G - 1];
+    n += __popcll(__ballot(i < G && at <= row));
   }
-  return lo;
+  return n > 0 ? n - 1 : 0;
 }
 
-// Group of rows visited in increasing order: a binary search for the first
-// row, then a step forward past the groups' ends as rows cross them (a load
-// only when a row leaves its group).  Same result as find_group for
-// non-decreasing offsets; g stays in [0, G) whatever the offsets hold.
+// Group of rows visited in increasing order, from the group of some row before
+// them: a step forward past the groups' ends as rows cross them (a load only
+// when a row leaves its group).  Same result as the search for non-decreasing
+// offsets; g stays in [0, G) whatever the offsets hold.
 struct GroupCursor {
-  int g = -1, g_end = 0;
+  int g, g_end = 0;
+  __device__ __forceinline__ explicit GroupCursor(int start) : g(start) {}
   __device__ __forceinline__ int at(const int32_t* __restrict__ off, int G, int row) {
-    if (g < 0 || row >= g_end) {
-      if (g < 0) g = find_group(off, G, row);
+    if (row >= g_end) {
       while (g + 1 < G && off[g + 1] <= row) ++g;
       g_end = g + 1 < G ? off[g + 1] : 0x7fffffff;
     }

@@ -210,3 +210,43 @@ def test_grouped_experts_with_empty_groups():
     rq, rs = pq.quant_act_grouped(X, inv, perm, off, k)
     np.testing.assert_array_equal(Asc, rs)
     np.testing.assert_array_equal(Aq, rq)
+
+
+# (K, k, M, groups): both sides of the line between the few-rows and the many-rows
+# kernels (1024 rows; 1024 x 768 channels), rows past the last 16-row block's
+# start filled by several workgroups (one to fifteen of them), more groups than a
+# wave has lanes, most of them empty, and the most groups there can be.
+LINE = [(768, 64, 1024, 1), (768, 64, 1025, 1), (32, 32, 1024, 1), (32, 0, 1039, 1), (2560, 64, 307, 1),
+        (2560, 64, 310, 1), (768, 64, 1024, 128), (768, 32, 1031, 300), (768, 64, 200, 65),
+        (2048, 96, 385, 70), (64, 32, 1300, 4096), (64, 32, 90, 4096)]
+
+
+@pytest.mark.parametrize("K,k,M,G", LINE)
+def test_kernel_choice_padding_and_group_search(K, k, M, G):
+    from paper_2609_22106_amd import prq
+    from tests.packing import pack_rows
+    rng = np.random.default_rng(K + M + G)
+    X = inputs.f32_to_bf16_bits((rng.standard_normal((M, K)) * 3).astype(np.float32))
+    perm = np.stack([rng.permutation(K) for _ in range(G)]).astype(np.int32)
+    inv = rng.uniform(0.1, 4.0, (G, K)).astype(np.float32)
+    off = None
+    if G > 1:   # a few crowded groups, the first and the last row's among empty ones
+        at = np.sort(rng.choice(np.arange(1, G - 1), 5, replace=False))
+        off = inputs.routed_offsets(np.bincount(rng.choice(at, M), minlength=G))
+        rq, rs = pq.quant_act_grouped(X, inv, perm, off, k)
+    else:
+        perm, inv = perm[0], inv[0]
+        rq, rs = pq.quant_act(X, inv, perm, k)
+    say("act_quant case: line", K, k, M, G)
+    Aq, Asc = _gpu_quant(X, K, k, inv, perm, offsets=off, G=G)
+    np.testing.assert_array_equal(Asc, rs)
+    np.testing.assert_array_equal(Aq, rq)
+    cb, sb = prq.prq_packed_act_bytes(M, K + k)
+    out = prq.PackedAct(torch.full((cb,), 0x5A, dtype=torch.uint8, device="cuda"),
+                        torch.full((sb,), 0xA5, dtype=torch.uint8, device="cuda"), M, K + k)
+    prq.prq_quant_act_packed(dev(X), K, k, dev(_pos(inv, perm)), dev(perm), out=out,
+                             group_offsets=None if off is None else dev(off), G=G)
+    torch.cuda.synchronize()
+    ep, es = pack_rows(rq, rs)
+    np.testing.assert_array_equal(host(out.Aps), es)
+    np.testing.assert_array_equal(host(out.Ap), ep)

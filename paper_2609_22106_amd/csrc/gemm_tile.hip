@@ -990,7 +990,8 @@ constexpr Shape kShapes[] = {{0, 256, 256, {1.0, 0.92, 0.92}, {0.85, 0.78, 0.78}
 // 256 x 256 tile alone on its CU = 65536): the busiest CU's tiles over the
 // shape's efficiency at that load.
 double shape_cost(const Shape& s, Efficiency which, long tiles, int cus) {
-  const long per_cu = (tiles + cus - 1) / cus;
+  const long per_cu = tiles < (1l << 30) ? (static_cast<uint32_t>(tiles) + cus - 1) / static_cast<uint32_t>(cus)
+                                        : (tiles + cus - 1) / cus;
   const double eff = which == kEffRowsSplit
                          ? s.eff_rows_split
                          : (which == kEffPacked ? s.eff_packed : s.eff_rows)[std::min<long>(per_cu, 3) - 1];
@@ -1017,15 +1018,23 @@ constexpr double kFillSteps = 3.0;      // pipeline fill, drain and Y store, in 
 constexpr double kLaunchUs = 3.0;       // a second launch
 constexpr double kReduceBytesPerUs = 5.0e6;
 
+//
+// The search is most of a small call's host time (N = 9728: 9 us with every
+// pair of regions priced in full), so a main region that costs the best plan
+// with the least that the rest can cost is not paired, and divisions are 32-bit where the tile counts fit.
 TilePlan plan_tile_gemm_by(int M, int N, int K_aug, int num_cus, Efficiency which, bool allow_split) {
   const int cus = std::max(num_cus, 1);
   const int ntiles = N / 16;
   const int steps = (K_aug + kStepK - 1) / kStepK;
-  auto cost = [&](const Shape& s, int cols16, int splits) {
+  constexpr int kCount = sizeof(kShapes) / sizeof(kShapes[0]);
+  long row_tiles[kCount];
+  for (int i = 0; i < kCount; ++i) row_tiles[i] = (M + kShapes[i].bm - 1) / kShapes[i].bm;
+  auto cost = [&](int shape, int cols16, int splits) {
     if (cols16 <= 0) return 0.0;
-    const long tiles = static_cast<long>((M + s.bm - 1) / s.bm) * ((cols16 * 16 + s.bn - 1) / s.bn);
-    const int per = (steps + splits - 1) / splits;
-    const long wgs = tiles * ((steps + per - 1) / per);
+    const Shape& s = kShapes[shape];
+    const long tiles = row_tiles[shape] * ((cols16 * 16 + s.bn - 1) / s.bn);
+    const int per = splits == 1 ? steps : (steps + splits - 1) / splits;
+    const long wgs = splits == 1 ? tiles : tiles * ((steps + per - 1) / per);
     // per-step time of the busiest CU: kStepUs256 per 256 x 256 tile alone
     const double step_us = kStepUs256 * shape_cost(s, which, wgs, cus) / 65536.0;
     double c = (per + kFillSteps) * step_us;
@@ -1036,32 +1045,37 @@ TilePlan plan_tile_gemm_by(int M, int N, int K_aug, int num_cus, Efficiency whic
   TilePlan best;
   double best_cost = 1e300;
   static const int kSplits[] = {1, 2, 3, 4, 6, 8};
-  for (const Shape& s : kShapes)
+  for (int i = 0; i < kCount; ++i)
     for (int sp : kSplits) {
       if (sp > 1 && (!allow_split || sp > steps)) break;
-      const double c = cost(s, ntiles, sp);
+      const double c = cost(i, ntiles, sp);
       if (c < best_cost) {
         best_cost = c;
         best = TilePlan{};
-        best.shape[0] = s.id;
+        best.shape[0] = kShapes[i].id;
         best.tiles[0] = ntiles;
         best.splits = sp;
       }
     }
-  for (const Shape& a : kShapes)
-    for (int main16 = a.bn / 16; main16 < ntiles; main16 += a.bn / 16)
-      for (const Shape& b : kShapes) {
-        const double c = cost(a, main16, 1) + cost(b, ntiles - main16, 1) + kLaunchUs;
+  const double least = 0.999999 * (steps + kFillSteps) * kStepUs256 / 65536.0 * 16.0 * M / cus;   // a 16-column tile
+  for (int i = 0; i < kCount; ++i)
+    for (int main16 = kShapes[i].bn / 16; main16 < ntiles; main16 += kShapes[i].bn / 16) {
+      const double main = cost(i, main16, 1);
+      // (the rest costs at least its area spread over every CU at full efficiency)
+      if (main + (ntiles - main16) * least + kLaunchUs >= best_cost) continue;
+      for (int j = 0; j < kCount; ++j) {
+        const double c = main + cost(j, ntiles - main16, 1) + kLaunchUs;
         if (c < best_cost) {
           best_cost = c;
           best = TilePlan{};
-          best.shape[0] = a.id;
-          best.shape[1] = b.id;
+          best.shape[0] = kShapes[i].id;
+          best.shape[1] = kShapes[j].id;
           best.tiles[0] = main16;
           best.tiles[1] = ntiles - main16;
           best.parts = 2;
         }
       }
+    }
   if (best.splits > 1) {   // the launcher's normalisation: every range non-empty
     const int per = (steps + best.splits - 1) / best.splits;
     best.splits = (steps + per - 1) / per;
@@ -1156,9 +1170,12 @@ hipError_t launch_grouped_gemm_tile_packed(const uint8_t* Ap, const uint8_t* Aps
                        N / 16, stream);
 }
 
-size_t tile_workspace_bytes(int M, int N, int K_aug, bool packed, int num_cus) {
-  const TilePlan plan = plan_tile_gemm(M, N, K_aug, num_cus, packed, true);
+static size_t plan_workspace_bytes(const TilePlan& plan, int M, int N) {
   return plan.splits > 1 ? static_cast<size_t>(plan.splits - 1) * M * N * sizeof(float) : 0;
+}
+
+size_t tile_workspace_bytes(int M, int N, int K_aug, bool packed, int num_cus) {
+  return plan_workspace_bytes(plan_tile_gemm(M, N, K_aug, num_cus, packed, true), M, N);
 }
 
 hipError_t launch_gemm_tile_planned(const uint8_t* Aq, const uint8_t* Asc, int M,
@@ -1169,11 +1186,11 @@ hipError_t launch_gemm_tile_planned(const uint8_t* Aq, const uint8_t* Asc, int M
   // workspace (the reduction moves float4s); otherwise the best plan without.
   const bool aligned = (reinterpret_cast<uintptr_t>(Y) & 15u) == 0 &&
                        (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
-  const size_t need = tile_workspace_bytes(M, N, K_aug, packed, num_cus);
-  const bool split = workspace && aligned && need > 0 && workspace_bytes >= need;
-  return launch_plan(Aq, Asc, M, Wp, Wps, N, K_aug, Y, packed,
-                     plan_tile_gemm(M, N, K_aug, num_cus, packed, split),
-                     static_cast<float*>(workspace), stream);
+  TilePlan plan = plan_tile_gemm(M, N, K_aug, num_cus, packed, true);
+  const size_t need = plan_workspace_bytes(plan, M, N);
+  if (need && !(workspace && aligned && workspace_bytes >= need))
+    plan = plan_tile_gemm(M, N, K_aug, num_cus, packed, false);
+  return launch_plan(Aq, Asc, M, Wp, Wps, N, K_aug, Y, packed, plan, static_cast<float*>(workspace), stream);
 }
 
 hipError_t launch_gemm_tile_split(const uint8_t* Aq, const uint8_t* Asc, int M, const uint8_t* Wp,

@@ -123,6 +123,19 @@ def _stream(stream):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+# The current stream's handle without a torch.cuda.Stream object around it (3.5 of
+# the 11 us that a call took on the host).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_cur_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+def _stream_of_call(stream):
+    """_stream for calls that have been given GPU tensors."""
+    if stream is None and _raw_stream is not None and _cur_device is not None:
+        return _raw_stream(_cur_device())
+    return _stream(stream)
+
+
 # --------------------------------------------------------------- prepare ---
 def prq_prepare(W_bf16, Xcal_bf16, alpha, k_tail, scale_mode="smooth", with_col_err=False,
                 scale_search=False):
@@ -236,6 +249,67 @@ def _on_gpu(**tensors):
 
 
 _BF16_LIKE = (torch.int16, torch.uint16, torch.bfloat16)
+_U8, _F32, _I32 = torch.uint8, torch.float32, torch.int32
+
+
+# The same checks in one expression per tensor, for the calls of an inference
+# step: whatever does not pass goes through the checks above, which say why.
+def _is(t, dtype, shape):
+    return (type(t) is torch.Tensor and t.dtype is dtype and t.shape == shape and t.is_cuda
+            and t.is_contiguous())
+
+
+def _holds(t, dtype, numel):
+    return (type(t) is torch.Tensor and t.dtype is dtype and t.numel() >= numel and t.is_cuda
+            and t.is_contiguous())
+
+
+def _packed_sizes(blocks, K_aug):
+    """Code and scale bytes of `blocks` 16-row blocks (prq_packed_act_bytes,
+    prq_packed_weight_bytes), or (None, None) where those refuse K_aug."""
+    if K_aug <= 0 or K_aug % 32 or K_aug > 65536:
+        return None, None
+    steps = (K_aug + 127) // 128
+    return blocks * steps * 1024, blocks * ((steps + 3) // 4) * 256
+
+
+def _weight_fits(W):
+    if not (1 <= W.E <= 4096 and W.N > 0 and W.N % 16 == 0):
+        return False
+    cb, sb = _packed_sizes(W.E * (W.N // 16), W.K_aug)
+    return cb is not None and _holds(W.Wp, _U8, cb) and _holds(W.Wps, _U8, sb)
+
+
+def _packed_act_fits(A):
+    cb, sb = _packed_sizes((A.M + 15) // 16, A.K_aug) if A.M >= 0 else (None, None)
+    return cb is not None and _holds(A.Ap, _U8, cb) and _holds(A.Aps, _U8, sb)
+
+
+def _scales_fit(inv_scale_pos, perm, group_offsets, G, K):
+    return ((inv_scale_pos is None or _holds(inv_scale_pos, _F32, G * K))
+            and (perm is None or _holds(perm, _I32, G * K))
+            and (G <= 1 or (group_offsets is not None and _holds(group_offsets, _I32, G + 1))))
+
+
+def _workspace_arg(workspace):
+    """(address, bytes) of a workspace argument."""
+    if workspace is None:
+        return None, 0
+    if not _holds(workspace, _U8, 0):
+        _need(workspace, "workspace", torch.uint8)
+        _on_gpu(workspace=workspace)
+    return workspace.data_ptr(), workspace.numel()
+
+
+def _check_scales(inv_scale_pos, perm, group_offsets, G, K):
+    if inv_scale_pos is not None:
+        _need(inv_scale_pos, "inv_scale_pos", torch.float32, min_numel=G * K)
+    if perm is not None:
+        _need(perm, "perm", torch.int32, min_numel=G * K)
+    if G > 1:
+        if group_offsets is None:
+            raise ValueError("G > 1 needs group_offsets")
+        _need(group_offsets, "group_offsets", torch.int32, min_numel=G + 1)
 
 
 def prq_quant_act(X, K, k_tail, inv_scale_pos=None, perm=None, group_offsets=None, G=1,
@@ -253,21 +327,16 @@ def prq_quant_act(X, K, k_tail, inv_scale_pos=None, perm=None, group_offsets=Non
         Aq = torch.empty((M, K_aug // 2), dtype=torch.uint8, device=X.device)
     if Asc is None:
         Asc = torch.empty((M, K_aug // 32), dtype=torch.uint8, device=X.device)
-    _need(Aq, "Aq", torch.uint8, (M, K_aug // 2))
-    _need(Asc, "Asc", torch.uint8, (M, K_aug // 32))
-    if inv_scale_pos is not None:
-        _need(inv_scale_pos, "inv_scale_pos", torch.float32, min_numel=G * K)
-    if perm is not None:
-        _need(perm, "perm", torch.int32, min_numel=G * K)
-    if G > 1:
-        if group_offsets is None:
-            raise ValueError("G > 1 needs group_offsets")
-        _need(group_offsets, "group_offsets", torch.int32, min_numel=G + 1)
-    _on_gpu(X=X, Aq=Aq, Asc=Asc, inv_scale_pos=inv_scale_pos, perm=perm,
-            group_offsets=group_offsets if G > 1 else None)
+    if not (X.is_cuda and _is(Aq, _U8, (M, K_aug // 2)) and _is(Asc, _U8, (M, K_aug // 32))
+            and _scales_fit(inv_scale_pos, perm, group_offsets, G, K)):
+        _need(Aq, "Aq", torch.uint8, (M, K_aug // 2))
+        _need(Asc, "Asc", torch.uint8, (M, K_aug // 32))
+        _check_scales(inv_scale_pos, perm, group_offsets, G, K)
+        _on_gpu(X=X, Aq=Aq, Asc=Asc, inv_scale_pos=inv_scale_pos, perm=perm,
+                group_offsets=group_offsets if G > 1 else None)
     ld = X.stride(0) if M > 1 else K
-    st = _quant_act(_ptr(X), ld, M, K, k_tail, _ptr(inv_scale_pos), _ptr(perm), _ptr(group_offsets), G,
-                    _ptr(Aq), _ptr(Asc), _stream(stream))
+    st = _quant_act(X.data_ptr(), ld, M, K, k_tail, _ptr(inv_scale_pos), _ptr(perm), _ptr(group_offsets), G,
+                    Aq.data_ptr(), Asc.data_ptr(), _stream_of_call(stream))
     _check(st, "prq_quant_act")
     return Aq, Asc
 
@@ -285,6 +354,9 @@ class PackedWeight:
 
 
 def _check_gemm_operands(Aq, Asc, W, Y, M):
+    if (_is(Aq, _U8, (M, W.K_aug // 2)) and _is(Asc, _U8, (M, W.K_aug // 32)) and _is(Y, _F32, (M, W.N))
+            and _weight_fits(W)):
+        return
     _need(Aq, "Aq", torch.uint8, (M, W.K_aug // 2))
     _need(Asc, "Asc", torch.uint8, (M, W.K_aug // 32))
     _need(Y, "Y", torch.float32, (M, W.N))
@@ -331,15 +403,13 @@ def prq_gemm(Aq, Asc, W, Y=None, workspace=None, variant=GEMM_AUTO, splits=0, st
     if Y is None:
         Y = torch.empty((M, N), dtype=torch.float32, device=W.Wp.device)
     _check_gemm_operands(Aq, Asc, W, Y, M)
-    need = prq_gemm_workspace_bytes(M, N, K_aug, variant, splits)
-    if workspace is None and need:
-        workspace = torch.zeros(need, dtype=torch.uint8, device=W.Wp.device)
-    if workspace is not None:
-        _need(workspace, "workspace", torch.uint8)
-        _on_gpu(workspace=workspace)
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    st = _gemm_ex(_ptr(Aq), _ptr(Asc), M, _ptr(W.Wp), _ptr(W.Wps), N, K_aug, _ptr(Y),
-                  _ptr(workspace), ws_bytes, variant, splits, _stream(stream))
+    if workspace is None:
+        need = prq_gemm_workspace_bytes(M, N, K_aug, variant, splits)
+        if need:
+            workspace = torch.zeros(need, dtype=torch.uint8, device=W.Wp.device)
+    ws, ws_bytes = _workspace_arg(workspace)
+    st = _gemm_ex(Aq.data_ptr(), Asc.data_ptr(), M, W.Wp.data_ptr(), W.Wps.data_ptr(), N, K_aug,
+                  Y.data_ptr(), ws, ws_bytes, variant, splits, _stream_of_call(stream))
     _check(st, "prq_gemm")
     return Y
 
@@ -355,8 +425,8 @@ def prq_gemm_noalloc(Aq, Asc, W, Y, stream=None):
     if W.E != 1:
         raise ValueError("prq_gemm_noalloc takes a single weight (E = 1)")
     _check_gemm_operands(Aq, Asc, W, Y, M)
-    st = _gemm_noalloc(_ptr(Aq), _ptr(Asc), M, _ptr(W.Wp), _ptr(W.Wps), W.N, W.K_aug, _ptr(Y),
-                       _stream(stream))
+    st = _gemm_noalloc(Aq.data_ptr(), Asc.data_ptr(), M, W.Wp.data_ptr(), W.Wps.data_ptr(), W.N, W.K_aug,
+                       Y.data_ptr(), _stream_of_call(stream))
     _check(st, "prq_gemm_noalloc")
     return Y
 
@@ -398,21 +468,15 @@ def prq_quant_act_packed(X, K, k_tail, inv_scale_pos=None, perm=None, out=None, 
                         torch.empty(sb, dtype=torch.uint8, device=X.device), M, K_aug)
     if out.M != M or out.K_aug != K_aug:
         raise ValueError(f"out holds {out.M} rows of K_aug {out.K_aug}, expected {M} x {K_aug}")
-    out.check_sizes()
-    if inv_scale_pos is not None:
-        _need(inv_scale_pos, "inv_scale_pos", torch.float32, min_numel=G * K)
-    if perm is not None:
-        _need(perm, "perm", torch.int32, min_numel=G * K)
-    if G > 1:
-        if group_offsets is None:
-            raise ValueError("G > 1 needs group_offsets")
-        _need(group_offsets, "group_offsets", torch.int32, min_numel=G + 1)
-    _on_gpu(X=X, Ap=out.Ap, Aps=out.Aps, inv_scale_pos=inv_scale_pos, perm=perm,
-            group_offsets=group_offsets if G > 1 else None)
+    if not (X.is_cuda and _packed_act_fits(out) and _scales_fit(inv_scale_pos, perm, group_offsets, G, K)):
+        out.check_sizes()
+        _check_scales(inv_scale_pos, perm, group_offsets, G, K)
+        _on_gpu(X=X, Ap=out.Ap, Aps=out.Aps, inv_scale_pos=inv_scale_pos, perm=perm,
+                group_offsets=group_offsets if G > 1 else None)
     ld = X.stride(0) if M > 1 else K
-    st = _quant_act_packed(_ptr(X), ld, M, K, k_tail, _ptr(inv_scale_pos), _ptr(perm),
-                           _ptr(group_offsets) if G > 1 else None, G, _ptr(out.Ap), _ptr(out.Aps),
-                           _stream(stream))
+    st = _quant_act_packed(X.data_ptr(), ld, M, K, k_tail, _ptr(inv_scale_pos), _ptr(perm),
+                           _ptr(group_offsets) if G > 1 else None, G, out.Ap.data_ptr(), out.Aps.data_ptr(),
+                           _stream_of_call(stream))
     _check(st, "prq_quant_act_packed")
     return out
 
@@ -439,18 +503,20 @@ def prq_swiglu_quant(gate, up, K_aug, packed=False, out=None, stream=None):
                             torch.empty(sb, dtype=torch.uint8, device=gate.device), M, K_aug)
         if out.M != M or out.K_aug != K_aug:
             raise ValueError(f"out holds {out.M} rows of K_aug {out.K_aug}, expected {M} x {K_aug}")
-        out.check_sizes()
+        if not _packed_act_fits(out):
+            out.check_sizes()
         A, As = out.Ap, out.Aps
     else:
         if out is None:
             out = (torch.empty((M, K_aug // 2), dtype=torch.uint8, device=gate.device),
                    torch.empty((M, K_aug // 32), dtype=torch.uint8, device=gate.device))
         A, As = out
-        _need(A, "Aq", torch.uint8, (M, K_aug // 2))
-        _need(As, "Asc", torch.uint8, (M, K_aug // 32))
+        if not (_is(A, _U8, (M, K_aug // 2)) and _is(As, _U8, (M, K_aug // 32))):
+            _need(A, "Aq", torch.uint8, (M, K_aug // 2))
+            _need(As, "Asc", torch.uint8, (M, K_aug // 32))
     _on_gpu(gate=gate, up=up, A=A, As=As)
     fn = _swiglu_quant_packed if packed else _swiglu_quant
-    st = fn(_ptr(gate), _ptr(up), ld, M, K_aug, _ptr(A), _ptr(As), _stream(stream))
+    st = fn(gate.data_ptr(), up.data_ptr(), ld, M, K_aug, A.data_ptr(), As.data_ptr(), _stream_of_call(stream))
     _check(st, "prq_swiglu_quant_packed" if packed else "prq_swiglu_quant")
     return out
 
@@ -470,16 +536,14 @@ def prq_gemm_packed(A, W, Y=None, workspace=None, stream=None):
     M, N = A.M, W.N
     if Y is None:
         Y = torch.empty((M, N), dtype=torch.float32, device=W.Wp.device)
-    _need(Y, "Y", torch.float32, (M, N))
-    A.check_sizes()
-    W.check_sizes()
-    _on_gpu(Ap=A.Ap, Aps=A.Aps, Y=Y, Wp=W.Wp, Wps=W.Wps)
-    if workspace is not None:
-        _need(workspace, "workspace", torch.uint8)
-        _on_gpu(workspace=workspace)
-    ws_bytes = workspace.numel() if workspace is not None else 0
-    st = _gemm_packed(_ptr(A.Ap), _ptr(A.Aps), M, _ptr(W.Wp), _ptr(W.Wps), N, W.K_aug, _ptr(Y),
-                      _ptr(workspace), ws_bytes, _stream(stream))
+    if not (_is(Y, _F32, (M, N)) and _packed_act_fits(A) and _weight_fits(W)):
+        _need(Y, "Y", torch.float32, (M, N))
+        A.check_sizes()
+        W.check_sizes()
+        _on_gpu(Ap=A.Ap, Aps=A.Aps, Y=Y, Wp=W.Wp, Wps=W.Wps)
+    ws, ws_bytes = _workspace_arg(workspace)
+    st = _gemm_packed(A.Ap.data_ptr(), A.Aps.data_ptr(), M, W.Wp.data_ptr(), W.Wps.data_ptr(), N, W.K_aug,
+                      Y.data_ptr(), ws, ws_bytes, _stream_of_call(stream))
     _check(st, "prq_gemm_packed")
     return Y
 
@@ -492,13 +556,15 @@ def prq_grouped_gemm_packed(A, group_offsets, W, Y=None, stream=None):
     M, E, N = A.M, W.E, W.N
     if Y is None:
         Y = torch.empty((M, N), dtype=torch.float32, device=W.Wp.device)
-    _need(Y, "Y", torch.float32, (M, N))
-    _need(group_offsets, "group_offsets", torch.int32, (E + 1,))
-    A.check_sizes()
-    W.check_sizes()
-    _on_gpu(Ap=A.Ap, Aps=A.Aps, Y=Y, Wp=W.Wp, Wps=W.Wps, group_offsets=group_offsets)
-    st = _ggemm_packed(_ptr(A.Ap), _ptr(A.Aps), _ptr(group_offsets), E, M, _ptr(W.Wp), _ptr(W.Wps),
-                       N, W.K_aug, _ptr(Y), _stream(stream))
+    if not (_is(Y, _F32, (M, N)) and _is(group_offsets, _I32, (E + 1,)) and _packed_act_fits(A)
+            and _weight_fits(W)):
+        _need(Y, "Y", torch.float32, (M, N))
+        _need(group_offsets, "group_offsets", torch.int32, (E + 1,))
+        A.check_sizes()
+        W.check_sizes()
+        _on_gpu(Ap=A.Ap, Aps=A.Aps, Y=Y, Wp=W.Wp, Wps=W.Wps, group_offsets=group_offsets)
+    st = _ggemm_packed(A.Ap.data_ptr(), A.Aps.data_ptr(), group_offsets.data_ptr(), E, M, W.Wp.data_ptr(),
+                       W.Wps.data_ptr(), N, W.K_aug, Y.data_ptr(), _stream_of_call(stream))
     _check(st, "prq_grouped_gemm_packed")
     return Y
 
@@ -514,14 +580,12 @@ def prq_grouped_gemm(Aq, Asc, group_offsets, W, Y=None, workspace=None, variant=
     E, N, K_aug = W.E, W.N, W.K_aug
     if Y is None:
         Y = torch.empty((M, N), dtype=torch.float32, device=W.Wp.device)
-    _need(group_offsets, "group_offsets", torch.int32, (E + 1,))
+    if not _is(group_offsets, _I32, (E + 1,)):
+        _need(group_offsets, "group_offsets", torch.int32, (E + 1,))
     _check_gemm_operands(Aq, Asc, W, Y, M)
     _on_gpu(group_offsets=group_offsets)
-    if workspace is not None:
-        _need(workspace, "workspace", torch.uint8)
-        _on_gpu(workspace=workspace)
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    st = _ggemm_ex(_ptr(Aq), _ptr(Asc), _ptr(group_offsets), E, M, _ptr(W.Wp), _ptr(W.Wps), N,
-                   K_aug, _ptr(Y), _ptr(workspace), ws_bytes, variant, _stream(stream))
+    ws, ws_bytes = _workspace_arg(workspace)
+    st = _ggemm_ex(Aq.data_ptr(), Asc.data_ptr(), group_offsets.data_ptr(), E, M, W.Wp.data_ptr(),
+                   W.Wps.data_ptr(), N, K_aug, Y.data_ptr(), ws, ws_bytes, variant, _stream_of_call(stream))
     _check(st, "prq_grouped_gemm")
     return Y

@@ -365,3 +365,22 @@ def test_swiglu_quant_rejects_bad_arguments_before_the_gpu():
         assert fn(a, a, 68, 4, 64, a, a, None) == prq.PRQ_EALIGN
         assert fn(a, a, 70000, 4, 65568, a, a, None) == prq.PRQ_EUNSUPPORTED
     assert prq._swiglu_quant_packed(256, 256, 64, 4, 64, 256, 260, None) == prq.PRQ_EALIGN
+
+
+def test_binding_sizes_equal_the_librarys():
+    """The sizes the binding checks operands against, computed without a call,
+    and what the library says, refusals included."""
+    rng = np.random.default_rng(3)
+    for K_aug in [0, 16, 32, 96, 128, 160, 4192, 9984, 65536, 65568, *(32 * rng.integers(1, 2049, 40)).tolist()]:
+        for M in (0, 1, 15, 16, 17, 8192):
+            try:
+                want = prq.prq_packed_act_bytes(M, K_aug)
+            except prq.PRQError:
+                want = (None, None)
+            assert prq._packed_sizes((M + 15) // 16, K_aug) == want, (M, K_aug)
+        for E, N in ((1, 16), (3, 2560), (4096, 32)):
+            try:
+                want = prq.prq_packed_weight_bytes(E, N, K_aug)
+            except prq.PRQError:
+                want = (None, None)
+            assert prq._packed_sizes(E * (N // 16), K_aug) == want, (E, N, K_aug)

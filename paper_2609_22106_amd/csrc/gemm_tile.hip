@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 
 #include "mx_device.hpp"
@@ -172,7 +173,7 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
     const int32_t* __restrict__ off, int E, int n_mtiles, int tile_base, int region_tiles,
     const uint8_t* __restrict__ Wp,
     const uint8_t* __restrict__ Wps, int N, int K_aug, float* __restrict__ Y, int splits,
-    int split_steps, float* __restrict__ ws, int group_rows) {
+    int split_steps, float* __restrict__ ws, int group_rows, int stream_y) {
   using L = TileStage<kBM, kBN, kAMode>;
   constexpr bool kPackedA = kAMode == kAPacked;
   constexpr int kWaves = kWM * kWN;
@@ -575,17 +576,29 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_tile_kernel(
   // Element q of a lane's fragment is C[8 (q / 4) + 4 (l / 32) + q % 4][l % 32]:
   // activation row, feature column (32 lanes store 128 contiguous bytes).
   float* const dst = split == 0 ? Y : ws + static_cast<int64_t>(split - 1) * M * N;
+  auto store = [&](auto tc) {
 #pragma unroll
-  for (int i = 0; i < kFM; ++i)
+    for (int i = 0; i < kFM; ++i)
 #pragma unroll
-    for (int j = 0; j < kFN; ++j) {
-      const int n = t0 * 16 + wn * kTN + j * 32 + (lane & 31);
+      for (int j = 0; j < kFN; ++j) {
+        const int n = t0 * 16 + wn * kTN + j * 32 + (lane & 31);
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int m = row_begin + wm * kTM + i * 32 + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
-        if (m >= row_lo && m < row_end && n < n_end) dst[static_cast<int64_t>(m) * N + n] = acc[i][j][q];
+        for (int q = 0; q < 16; ++q) {
+          const int m = row_begin + wm * kTM + i * 32 + 8 * (q >> 2) + 4 * (lane >> 5) + (q & 3);
+          if (m >= row_lo && m < row_end && n < n_end) {
+            float* const at = dst + static_cast<int64_t>(m) * N + n;
+            if constexpr (decltype(tc)::value) __builtin_nontemporal_store(acc[i][j][q], at);
+            else *at = acc[i][j][q];
+          }
+        }
       }
-    }
+  };
+  if constexpr (kBN == 320) {   // (its calls are large: not worth the second store loop's registers)
+    store(IntC<0>{});
+  } else {
+    if (stream_y) store(IntC<1>{});   // uniform
+    else store(IntC<0>{});
+  }
 }
 
 // Grouped (MoE) tile GEMM on a packed activation, persistent and pipelined
@@ -909,7 +922,7 @@ hipError_t launch_shape_scales(const uint8_t* Aq, const uint8_t* Asc, int M, con
   if (off) {
     gemm_tile_kernel<kBM, kBN, kWM, kWN, kNS, true, kAMode><<<grid, kWM * kWN * 64, 0, stream>>>(
         Aq, Asc, M, off, E, n_mtiles, tile_base, region_tiles, Wp, Wps, N, K_aug, Y, 1,
-        split_steps, nullptr, 0);
+        split_steps, nullptr, 0, 0);
   } else {
     // Grouped tile order (measured, weights rotated, M x N x (K + k)): for 256-row
     // tiles always -- 4096 x 9728 x 2624 in 256 x 320, 77.0 -> 73.6 us; 4096 x
@@ -918,9 +931,18 @@ hipError_t launch_shape_scales(const uint8_t* Aq, const uint8_t* Asc, int M, con
     // 9984: 31.6 -> 28.8 us; 2048 x 2560 went 44.4 -> 51.5, 512 and 4096 x 1024
     // unchanged).
     const int group_rows = kBM == 256 || n_mtiles <= 8 ? 4 : 0;
+    // Non-temporal Y stores where all of Y stays below the L2s' 32 MB: ordinary
+    // ones leave it dirty there, and the kernel ends only when it has been written
+    // back (us, non-temporal / ordinary, and with an elementwise pass over Y after:
+    // 4096 x 1024 x 2624 11.5 / 13.4, 22.0 / 23.4; 1537 x 2560 x 4192 20.0 / 22.0,
+    // 26.6 / 28.2; 100 x 9728 x 2624 12.3 / 12.5, 15.4 / 15.9).  A larger Y is evicted
+    // as it is written either way, and its reader finds less of it in the caches
+    // (2048 x 2560 x 9984 42.6 / 43.0, 50.8 / 50.1; 4096 x 9728 x 2624 77.5 / 74.0,
+    // 125 / 118).  Partial sums are read back at once: ordinary.
+    const int stream_y = splits == 1 && static_cast<int64_t>(M) * N <= 5000000;
     gemm_tile_kernel<kBM, kBN, kWM, kWN, kNS, false, kAMode><<<grid, kWM * kWN * 64, 0, stream>>>(
         Aq, Asc, M, nullptr, 1, n_mtiles, tile_base, region_tiles, Wp, Wps, N, K_aug, Y, splits,
-        split_steps, ws, group_rows);
+        split_steps, ws, group_rows, stream_y);
   }
   hipError_t err = hipGetLastError();
   if (err != hipSuccess || splits == 1) return err;
@@ -960,52 +982,45 @@ hipError_t launch_region(const uint8_t* Aq, const uint8_t* Asc, int M, const int
   }
 }
 
+// Time of one tile shape over a call, in us:
+//   launch + (K steps + fill) * rate(u) + store * M * N / 10^6,
+//   rate(u) = whole * ceil(u) + spread * u + (128 x 128: pair * ceil(u / 2),
+//                                             else: pair * min(u, 1)),
+// u = workgroups / CUs.  A 128 x 128 workgroup leaves room for a second one on its
+// CU.  Fitted to the forced shapes over 17 row counts (66 .. 8192) of 9 (N, K + k)
+// from 2048 x 832 to 2560 x 9984, each layout (weights rotated; mean error 3 %; the
+// shape it picks is 0.2 % slower than the best one on average and 7 % at most,
+// where busiest-CU efficiencies by load class were 2 % and 34 %: 1537 x 9728 x 2624
+// 43.1 -> 35.2 us, 768 x 1936 x 5344 19.4 -> 14.5, 2500 x 2560 x 9984 47.7 -> 41.7).
+struct ShapeTime {
+  double launch, fill, whole, spread, pair, store;
+};
+// 256 x 320 (8 waves, 64 x 160 each, 3 stages) beats every other plan where it
+// fills the CUs evenly -- 8192 x 2560 x 9984 in one round of 256 tiles, 106 against
+// 120 us for 256 x 256 over 2048 columns and 128 x 128 over the rest.
 struct Shape {
   int id, bm, bn;
-  // Throughput per tile area by the most tiles any CU runs (1, 2, 3 or more),
-  // relative to one 256 x 256 tile of a packed A per CU.  Packed: fitted to the
-  // down_proj sweep (M = 1024 .. 8192, N = 2560, K + k = 9984, weights rotated):
-  // 128 x 128 workgroups fit two to a CU and hide each other's latency, so two per
-  // CU run far better than one.  Row-major: the packed factors over the measured
-  // ratio of the two layouts (half-line code loads): 1.18, 1.27, 1.26, 1.10.
-  double eff_packed[3];
-  double eff_rows[3];
-  // Row-major calls decide whether to split along K by these, whatever the loads:
-  // the workspace that a call needs (and prq_gemm_noalloc's limit on it) stays
-  // what callers have sized theirs for.
-  double eff_rows_split;
+  ShapeTime packed, rows;
+  // Throughput per tile area behind the workspace rule (see workspace_splits): by
+  // the most tiles any CU runs (1, 2, 3 or more) of a packed A, and of a row-major.
+  double eff_packed[3], eff_rows;
 };
-enum Efficiency { kEffPacked, kEffRows, kEffRowsSplit };
-// 256 x 320 (8 waves, 64 x 160 each, 3 stages): where it fills the CUs evenly
-// it beats every other plan -- 8192 x 2560 x 9984 in one round of 256 tiles,
-// 106 against 120 us for 256 x 256 over 2048 columns and 128 x 128 over the
-// rest; 4096 x 9728 x 2624, 80 against 93 us -- and loses elsewhere (half-empty
-// rounds); its factors are set to pick it exactly there.
-constexpr Shape kShapes[] = {{0, 256, 256, {1.0, 0.92, 0.92}, {0.85, 0.78, 0.78}, 1.0},
-                             {1, 256, 128, {0.73, 0.87, 0.80}, {0.58, 0.69, 0.63}, 0.63},
-                             {2, 128, 128, {0.58, 0.81, 0.68}, {0.46, 0.64, 0.54}, 0.5},
-                             {3, 256, 320, {0.9, 0.9, 0.85}, {0.82, 0.82, 0.77}, 0.5}};
-
-// Cost of `tiles` tiles of shape s on `cus` CUs in tile-area units (one
-// 256 x 256 tile alone on its CU = 65536): the busiest CU's tiles over the
-// shape's efficiency at that load.
-double shape_cost(const Shape& s, Efficiency which, long tiles, int cus) {
-  const long per_cu = tiles < (1l << 30) ? (static_cast<uint32_t>(tiles) + cus - 1) / static_cast<uint32_t>(cus)
-                                        : (tiles + cus - 1) / cus;
-  const double eff = which == kEffRowsSplit
-                         ? s.eff_rows_split
-                         : (which == kEffPacked ? s.eff_packed : s.eff_rows)[std::min<long>(per_cu, 3) - 1];
-  return per_cu * static_cast<double>(s.bm) * s.bn / eff;
-}
+constexpr Shape kShapes[] = {
+    {0, 256, 256, {2.36, 12.653, 0.462, 0.395, -0.113, 0.182}, {1.326, 12.859, 0.584, 0.402, -0.043, 0.156},
+     {1, 0.92, 0.92}, 1},
+    {1, 256, 128, {3.876, 12.767, 0.284, 0.252, -0.13, 0.241}, {2.57, 13.095, 0.391, 0.267, -0.035, 0.101},
+     {0.73, 0.87, 0.8}, 0.63},
+    {2, 128, 128, {1.887, 14.704, 0.167, 0.072, 0.037, 0}, {2.247, 10.736, 0.229, 0.089, 0.063, 0},
+     {0.58, 0.81, 0.68}, 0.5},
+    {3, 256, 320, {1.434, 13.064, 0.561, 0.449, -0.086, 0.156}, {1.315, 9.242, 0.856, 0.369, -0.112, 0.288},
+     {0.9, 0.9, 0.85}, 0.5}};
+constexpr int kShapeCount = sizeof(kShapes) / sizeof(kShapes[0]);
 
 // Plan of a dense tile GEMM: one shape over all N columns (optionally split
 // along K), or a main region of whole column tiles in one shape and the
 // remaining columns in another, so that each launch fills the CUs in whole
-// rounds (M = 8192, N = 2560: 256 tiles of 256 x 256 over 2048 columns, then
-// 256 tiles of 128 x 128).  Modelled time: workgroup rounds x (K steps per
-// workgroup + a fixed pipeline fill and store cost) x the shape's measured
-// time per step, plus a fixed cost for a second launch, or for split-K the
-// reduction (a launch plus the partial sums written, read and added).
+// rounds (M = 8192, N = 3376: 128 x 128 over the columns that 256-wide tiles would
+// leave to a nearly empty round).
 struct TilePlan {
   int shape[2] = {2, 2};
   int tiles[2] = {0, 0};   // 16-column tiles of each region
@@ -1013,58 +1028,62 @@ struct TilePlan {
   int splits = 1;          // K ranges (single region only)
 };
 
-constexpr double kStepUs256 = 0.9;      // one K step of a 256 x 256 tile in a full round
-constexpr double kFillSteps = 3.0;      // pipeline fill, drain and Y store, in steps
-constexpr double kLaunchUs = 3.0;       // a second launch
-constexpr double kReduceBytesPerUs = 5.0e6;
+constexpr int kSplits[] = {1, 2, 3, 4, 6, 8};
+constexpr double kSecondLaunchUs = 4.0;   // of a second region beyond the fit's own launch cost
+constexpr double kReduceUs = 4.5;         // the split's reduction: a launch and the first partials
+constexpr double kReduceUsPerMb = 0.13;   // and the partial sums read, Y written (68 measured splits)
 
-//
-// The search is most of a small call's host time (N = 9728: 9 us with every
-// pair of regions priced in full), so a main region that costs the best plan
-// with the least that the rest can cost is not paired, and divisions are 32-bit where the tile counts fit.
-TilePlan plan_tile_gemm_by(int M, int N, int K_aug, int num_cus, Efficiency which, bool allow_split) {
-  const int cus = std::max(num_cus, 1);
+// Split count with every K range non-empty, as the launcher makes it.
+int whole_splits(int steps, int splits) {
+  const int per = (steps + splits - 1) / splits;
+  return (steps + per - 1) / per;
+}
+
+size_t split_bytes(int splits, int M, int N) {
+  return static_cast<size_t>(splits - 1) * M * N * sizeof(float);
+}
+
+// The plan of least modelled time among those whose partial sums fit `room` bytes.
+// The search is much of a small call's host time, so a main region that costs the
+// best plan by itself is not paired, and divisions are 32-bit.
+TilePlan plan_tile_gemm(int M, int N, int K_aug, int num_cus, bool packed, size_t room) {
+  const double per_cu = 1.0 / std::max(num_cus, 1);
   const int ntiles = N / 16;
   const int steps = (K_aug + kStepK - 1) / kStepK;
-  constexpr int kCount = sizeof(kShapes) / sizeof(kShapes[0]);
-  long row_tiles[kCount];
-  for (int i = 0; i < kCount; ++i) row_tiles[i] = (M + kShapes[i].bm - 1) / kShapes[i].bm;
-  auto cost = [&](int shape, int cols16, int splits) {
-    if (cols16 <= 0) return 0.0;
+  double row_tiles[kShapeCount];
+  for (int i = 0; i < kShapeCount; ++i) row_tiles[i] = (M + kShapes[i].bm - 1) / kShapes[i].bm * per_cu;
+  auto cost = [&](int shape, int cols16, int per, int ranges) {
     const Shape& s = kShapes[shape];
-    const long tiles = row_tiles[shape] * ((cols16 * 16 + s.bn - 1) / s.bn);
-    const int per = splits == 1 ? steps : (steps + splits - 1) / splits;
-    const long wgs = splits == 1 ? tiles : tiles * ((steps + per - 1) / per);
-    // per-step time of the busiest CU: kStepUs256 per 256 x 256 tile alone
-    const double step_us = kStepUs256 * shape_cost(s, which, wgs, cus) / 65536.0;
-    double c = (per + kFillSteps) * step_us;
-    if (splits > 1)   // partials written, then Y and the partials read and Y written
-      c += kLaunchUs + 2.0 * ((steps + per - 1) / per) * 4.0 * M * N / kReduceBytesPerUs;
-    return c;
+    const ShapeTime& t = packed ? s.packed : s.rows;
+    const int col16 = s.bn / 16;
+    const double u = row_tiles[shape] * ((cols16 + col16 - 1) / col16) * ranges;
+    const double rate = t.whole * std::ceil(u - 1e-9) + t.spread * u +
+                        t.pair * (shape == 2 ? std::ceil(0.5 * u - 1e-9) : std::min(u, 1.0));
+    return t.launch + (per + t.fill) * rate + t.store * 16e-6 * M * cols16;
   };
   TilePlan best;
   double best_cost = 1e300;
-  static const int kSplits[] = {1, 2, 3, 4, 6, 8};
-  for (int i = 0; i < kCount; ++i)
+  for (int i = 0; i < kShapeCount; ++i)
     for (int sp : kSplits) {
-      if (sp > 1 && (!allow_split || sp > steps)) break;
-      const double c = cost(i, ntiles, sp);
+      if (sp > steps) break;
+      const int ranges = whole_splits(steps, sp);
+      if (ranges > 1 && split_bytes(ranges, M, N) > room) break;
+      double c = cost(i, ntiles, (steps + sp - 1) / sp, ranges);
+      if (ranges > 1) c += kReduceUs + kReduceUsPerMb * 4e-6 * M * N * (ranges + 1);
       if (c < best_cost) {
         best_cost = c;
         best = TilePlan{};
         best.shape[0] = kShapes[i].id;
         best.tiles[0] = ntiles;
-        best.splits = sp;
+        best.splits = ranges;
       }
     }
-  const double least = 0.999999 * (steps + kFillSteps) * kStepUs256 / 65536.0 * 16.0 * M / cus;   // a 16-column tile
-  for (int i = 0; i < kCount; ++i)
+  for (int i = 0; i < kShapeCount; ++i)
     for (int main16 = kShapes[i].bn / 16; main16 < ntiles; main16 += kShapes[i].bn / 16) {
-      const double main = cost(i, main16, 1);
-      // (the rest costs at least its area spread over every CU at full efficiency)
-      if (main + (ntiles - main16) * least + kLaunchUs >= best_cost) continue;
-      for (int j = 0; j < kCount; ++j) {
-        const double c = main + cost(j, ntiles - main16, 1) + kLaunchUs;
+      const double main = cost(i, main16, steps, 1) + kSecondLaunchUs;
+      if (main >= best_cost) break;   // wider main regions cost no less
+      for (int j = 0; j < kShapeCount; ++j) {
+        const double c = main + cost(j, ntiles - main16, steps, 1);
         if (c < best_cost) {
           best_cost = c;
           best = TilePlan{};
@@ -1076,20 +1095,58 @@ TilePlan plan_tile_gemm_by(int M, int N, int K_aug, int num_cus, Efficiency whic
         }
       }
     }
-  if (best.splits > 1) {   // the launcher's normalisation: every range non-empty
-    const int per = (steps + best.splits - 1) / best.splits;
-    best.splits = (steps + per - 1) / per;
-  }
   return best;
 }
 
-TilePlan plan_tile_gemm(int M, int N, int K_aug, int num_cus, bool packed, bool allow_split) {
-  if (packed) return plan_tile_gemm_by(M, N, K_aug, num_cus, kEffPacked, allow_split);
-  if (allow_split) {
-    const TilePlan split = plan_tile_gemm_by(M, N, K_aug, num_cus, kEffRowsSplit, true);
-    if (split.splits > 1) return split;
-  }
-  return plan_tile_gemm_by(M, N, K_aug, num_cus, kEffRows, false);
+// The split count whose partial sums a call's workspace holds, which callers have
+// sized theirs for (and prq_gemm_noalloc's limit goes by): a rule of its own, so
+// that it stays when the plans above are refitted; a call never uses more.  The
+// cheapest of one shape with a split, or two column regions, by rounds of the
+// busiest CU's tiles x (K steps per workgroup + a fixed fill) over the efficiency
+// at that load, plus a second launch or the reduction.
+int workspace_splits(int M, int N, int K_aug, int num_cus, bool packed) {
+  constexpr double kStepUs256 = 0.9, kFillSteps = 3.0, kLaunchUs = 3.0, kReduceBytesPerUs = 5.0e6;
+  const int cus = std::max(num_cus, 1);
+  const int ntiles = N / 16;
+  const int steps = (K_aug + kStepK - 1) / kStepK;
+  long row_tiles[kShapeCount];
+  for (int i = 0; i < kShapeCount; ++i) row_tiles[i] = (M + kShapes[i].bm - 1) / kShapes[i].bm;
+  auto cost = [&](int shape, int cols16, int splits) {
+    const Shape& s = kShapes[shape];
+    const long tiles = row_tiles[shape] * ((cols16 * 16 + s.bn - 1) / s.bn);
+    const int per = splits == 1 ? steps : (steps + splits - 1) / splits;
+    const long wgs = splits == 1 ? tiles : tiles * ((steps + per - 1) / per);
+    const long per_cu = wgs < (1l << 30) ? (static_cast<uint32_t>(wgs) + cus - 1) / static_cast<uint32_t>(cus)
+                                         : (wgs + cus - 1) / cus;
+    const double eff = packed ? s.eff_packed[std::min<long>(per_cu, 3) - 1] : s.eff_rows;
+    const double step_us = kStepUs256 * (per_cu * static_cast<double>(s.bm) * s.bn / eff) / 65536.0;
+    double c = (per + kFillSteps) * step_us;
+    if (splits > 1)   // partials written, then Y and the partials read and Y written
+      c += kLaunchUs + 2.0 * ((steps + per - 1) / per) * 4.0 * M * N / kReduceBytesPerUs;
+    return c;
+  };
+  int best = 1;
+  double best_cost = 1e300;
+  for (int i = 0; i < kShapeCount; ++i)
+    for (int sp : kSplits) {
+      if (sp > steps) break;
+      const double c = cost(i, ntiles, sp);
+      if (c < best_cost) {
+        best_cost = c;
+        best = sp;
+      }
+    }
+  if (best == 1) return 1;
+  const double least = 0.999999 * (steps + kFillSteps) * kStepUs256 / 65536.0 * 16.0 * M / cus;   // a 16-column tile
+  for (int i = 0; i < kShapeCount; ++i)
+    for (int main16 = kShapes[i].bn / 16; main16 < ntiles; main16 += kShapes[i].bn / 16) {
+      const double main = cost(i, main16, 1);
+      // (the rest costs at least its area spread over every CU at full efficiency)
+      if (main + (ntiles - main16) * least + kLaunchUs >= best_cost) continue;
+      for (int j = 0; j < kShapeCount; ++j)
+        if (main + cost(j, ntiles - main16, 1) + kLaunchUs < best_cost) return 1;
+    }
+  return whole_splits(steps, best);
 }
 
 hipError_t launch_plan(const uint8_t* Aq, const uint8_t* Asc, int M, const uint8_t* Wp,
@@ -1170,12 +1227,8 @@ hipError_t launch_grouped_gemm_tile_packed(const uint8_t* Ap, const uint8_t* Aps
                        N / 16, stream);
 }
 
-static size_t plan_workspace_bytes(const TilePlan& plan, int M, int N) {
-  return plan.splits > 1 ? static_cast<size_t>(plan.splits - 1) * M * N * sizeof(float) : 0;
-}
-
 size_t tile_workspace_bytes(int M, int N, int K_aug, bool packed, int num_cus) {
-  return plan_workspace_bytes(plan_tile_gemm(M, N, K_aug, num_cus, packed, true), M, N);
+  return split_bytes(workspace_splits(M, N, K_aug, num_cus, packed), M, N);
 }
 
 hipError_t launch_gemm_tile_planned(const uint8_t* Aq, const uint8_t* Asc, int M,
@@ -1186,10 +1239,13 @@ hipError_t launch_gemm_tile_planned(const uint8_t* Aq, const uint8_t* Asc, int M
   // workspace (the reduction moves float4s); otherwise the best plan without.
   const bool aligned = (reinterpret_cast<uintptr_t>(Y) & 15u) == 0 &&
                        (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
-  TilePlan plan = plan_tile_gemm(M, N, K_aug, num_cus, packed, true);
-  const size_t need = plan_workspace_bytes(plan, M, N);
-  if (need && !(workspace && aligned && workspace_bytes >= need))
-    plan = plan_tile_gemm(M, N, K_aug, num_cus, packed, false);
+  size_t room = workspace && aligned ? workspace_bytes : 0;
+  TilePlan plan = plan_tile_gemm(M, N, K_aug, num_cus, packed, room);
+  if (plan.splits > 1) {   // no more than the call's workspace rule, whatever it is given
+    const size_t rule = tile_workspace_bytes(M, N, K_aug, packed, num_cus);
+    if (split_bytes(plan.splits, M, N) > rule)
+      plan = plan_tile_gemm(M, N, K_aug, num_cus, packed, std::min(room, rule));
+  }
   return launch_plan(Aq, Asc, M, Wp, Wps, N, K_aug, Y, packed, plan, static_cast<float*>(workspace), stream);
 }
 

@@ -384,3 +384,18 @@ def test_binding_sizes_equal_the_librarys():
             except prq.PRQError:
                 want = (None, None)
             assert prq._packed_sizes(E * (N // 16), K_aug) == want, (E, N, K_aug)
+
+
+# (M, N, K_aug): K ranges of the row-major and the packed call's workspace rule.
+WORKSPACE_RULE = [(65, 2560, 9984, 8, 8), (333, 2560, 4192, 3, 3), (512, 2560, 9984, 3, 3),
+                  (1024, 2560, 9984, 3, 1), (1536, 2560, 9984, 1, 1), (768, 1936, 5344, 2, 2),
+                  (100, 1024, 2624, 7, 7), (4096, 9728, 2624, 1, 1), (300, 16, 65536, 8, 8),
+                  (2048, 2048, 832, 1, 1)]
+
+
+@pytest.mark.parametrize("M,N,K_aug,rows,packed", WORKSPACE_RULE)
+def test_workspace_rule_stays(M, N, K_aug, rows, packed):
+    """What callers have sized their workspaces for does not move with the plans."""
+    want = lambda r: HEAD + (r - 1) * M * N * 4 if r > 1 else 0  # noqa: E731
+    assert prq.prq_gemm_workspace_bytes(M, N, K_aug) == want(rows)
+    assert prq.prq_gemm_packed_workspace_bytes(M, N, K_aug) == want(packed)

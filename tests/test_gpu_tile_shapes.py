@@ -133,3 +133,38 @@ def test_tile_split_k(shape, packed, M, N, K_aug, splits):
     np.testing.assert_array_equal(outs[0], outs[1])
     assert_gemm_close(outs[0], pq.gemm(Aq, Asc, Wq, Wsc),
                       f"split shape {shape} packed {packed} {M}x{N}x{K_aug} / {splits}")
+
+
+# Planned calls (row-major, packed) without room for a split: one region and two;
+# Y just below and above the size that is stored non-temporally; the narrowest N,
+# fewer rows than a tile, more tiles than several rounds; N no multiple of a tile.
+PLANNED = [(66, 16, 1056), (70, 13824, 640), (300, 1936, 1312), (1220, 4096, 288), (1222, 4096, 288),
+           (1537, 9728, 416), (2500, 9728, 288), (4096, 6144, 160), (6000, 4112, 160), (8200, 272, 544)]
+
+
+@pytest.mark.parametrize("M,N,K_aug", PLANNED)
+@pytest.mark.parametrize("packed", [True, False])
+def test_planned_call_equals_forced_shape(packed, M, N, K_aug):
+    """Every tile shape adds a row's products in the same order, so an unsplit
+    planned call gives the bits of the 128 x 128 shape forced over all columns
+    (itself checked against the oracle above), wherever the planner cuts N."""
+    from paper_2609_22106_amd import prq
+    from tests.packing import pack_rows
+    rng = np.random.default_rng(M + N + K_aug)
+    Aq, Asc = inputs.random_mxfp4(rng, M, K_aug)
+    Wq, Wsc = inputs.random_mxfp4(rng, N, K_aug)
+    W = prq.prq_pack_weight(dev(Wq), dev(Wsc))
+    A, As = (map(dev, pack_rows(Aq, Asc)) if packed else (dev(Aq), dev(Asc)))
+    want, got = (torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda") for _ in range(2))
+    stream = torch.cuda.current_stream().cuda_stream
+    say("planned case:", packed, M, N, K_aug)
+    rc = _split_lib().prq_tune_gemm_tile_split(A.data_ptr(), As.data_ptr(), M, W.Wp.data_ptr(),
+                                               W.Wps.data_ptr(), N, K_aug, want.data_ptr(), 2, 1,
+                                               int(packed), 0, 0, stream)
+    assert rc == 0, rc
+    call = prq._gemm_packed if packed else prq._gemm
+    assert call(A.data_ptr(), As.data_ptr(), M, W.Wp.data_ptr(), W.Wps.data_ptr(), N, K_aug,
+                got.data_ptr(), None, 0, stream) == 0
+    torch.cuda.synchronize()
+    assert not torch.isnan(want).any()
+    assert torch.equal(want, got)

@@ -634,14 +634,6 @@ __global__ __launch_bounds__(kDmaThreads) void act_quant_dma_kernel(
   }
 }
 
-template <bool kGrouped, int kUnits, bool kPacked = false>
-void launch_lds(dim3 grid, size_t lds, hipStream_t stream, const uint16_t* X, int64_t ld_x,
-                int M, int K, int k_tail, const float* inv, const int32_t* perm,
-                const int32_t* offsets, int G, int rows_per_wg, uint8_t* Aq, uint8_t* Asc) {
-  act_quant_lds_kernel<kGrouped, kUnits, kPacked><<<grid, kLdsThreads, lds, stream>>>(
-      X, ld_x, M, K, k_tail, inv, perm, offsets, G, rows_per_wg, Aq, Asc);
-}
-
 // Rows per workgroup of the LDS kernel: two workgroups per CU, a whole number
 // of passes each, contiguous row ranges (inside one expert for most rows).
 int lds_rows_per_wg(int M, int units, int num_cus) {
@@ -649,6 +641,149 @@ int lds_rows_per_wg(int M, int units, int num_cus) {
   const int target = std::max(1, num_cus * 2);
   int rows_per_wg = std::max(1, (M + target - 1) / target);
   return (rows_per_wg + rpp - 1) / rpp * rpp;
+}
+
+// Many short rows (K < 2048): as the copy kernel, with a pass of R =
+// lds_rows_per_pass(K / 8) whole rows (at most 8 KiB) in a stage and one unit of
+// one of them per compute thread.  act_quant_lds_kernel, which took these rows,
+// stages through registers of the threads that also store the output: a load's
+// wait there waits for the stores before it, one memory round trip after another
+// per pass (32768 x 768 in 128 groups: row-major 22.5 us, here 18.7; packed 25.6
+// and 22.6; 12.6 at copy rate).
+constexpr int kShortStage = 8192, kShortStages = 4;
+
+template <bool kGrouped, bool kPacked>
+__global__ __launch_bounds__(kDmaThreads) void act_quant_short_kernel(
+    const uint16_t* __restrict__ X, int64_t ld_x, int M, int K, int k_tail,
+    const float* __restrict__ inv, const int32_t* __restrict__ perm,
+    const int32_t* __restrict__ offsets, int G, int rows_per_wg, uint8_t* __restrict__ Aq,
+    uint8_t* __restrict__ Asc) {
+  constexpr int kCpw = kShortStage / 1024 / kCopyWaves;   // copies per copy wave per pass
+  constexpr int kNS = kShortStages;
+  __shared__ __align__(16) uint8_t stg[kNS * kShortStage];
+  const int r0 = blockIdx.x * rows_per_wg;
+  const int r1 = min(M, r0 + rows_per_wg);
+  if (r0 >= r1) return;                            // uniform
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int units = K >> 3;
+  const int rpp = lds_rows_per_pass(units);
+  const int n = (r1 - r0 + rpp - 1) / rpp;         // passes
+  if (wave >= kComputeThreads / 64) {              // copy waves
+    const int cw = wave - kComputeThreads / 64;
+    const int row_bytes_x = 2 * K;
+    const int chunks = (rpp * row_bytes_x + 1023) >> 10;
+    const uint32_t stg_lds = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(PRQ_LPTR(stg)));
+    // This lane's 16 bytes of each of its copies: row of the pass, byte offset
+    // from the pass's first row (past the pass's rows: that row's start, into the
+    // stage's pad).
+    int vrow[kCpw];
+    int64_t voff[kCpw];
+#pragma unroll
+    for (int j = 0; j < kCpw; ++j) {
+      const int b = min(cw + j * kCopyWaves, chunks - 1) * 1024 + lane * 16;
+      vrow[j] = b / row_bytes_x;
+      voff[j] = vrow[j] < rpp ? vrow[j] * ld_x * 2 + (b - vrow[j] * row_bytes_x) : 0;
+    }
+    auto copy_pass = [&](int i) {                  // i clamped into the range
+      const int rb = r0 + min(i, n - 1) * rpp;
+      const uint8_t* const src = reinterpret_cast<const uint8_t*>(X + static_cast<int64_t>(rb) * ld_x);
+      const uint32_t st = stg_lds + static_cast<uint32_t>(i % kNS) * kShortStage;
+#pragma unroll
+      for (int j = 0; j < kCpw; ++j) {
+        const int c = min(cw + j * kCopyWaves, chunks - 1);
+        lds_copy16(src + (rb + vrow[j] < r1 ? voff[j] : 0), __builtin_amdgcn_readfirstlane(st + c * 1024));
+      }
+    };
+    for (int i = 0; i < kNS - 1; ++i) copy_pass(i);
+    for (int i = 0; i < n; ++i) {
+      wait_vmcnt_lgkm0<(kNS - 2) * kCpw>();        // pass i has landed
+      __builtin_amdgcn_s_barrier();
+      copy_pass(i + kNS - 1);                      // into the stage of pass i-1
+    }
+    __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8));   // no copy outlives the workgroup
+    return;
+  }
+
+  const int k_aug = K + k_tail;
+  const int64_t row_bytes = k_aug >> 1;
+  const int nb = k_aug >> 5;
+  const int tail_unit0 = (K - k_tail) >> 3;
+  const int steps = (k_aug + 127) >> 7;
+  const int sgroups = (steps + 3) >> 2;
+  const int ro = tid / units;                      // this thread's row within a pass
+  const int u = tid - ro * units;                  // and its unit
+  const int rot = (lane >> 3) & 3, rs = (4 - rot) & 3;   // LDS banks, as above
+  PackedUnit un;
+  dev::GroupCursor gc(kGrouped ? dev::wave_find_group(offsets, G, r0) : 0);
+  int cur_g = gc.g;
+  load_packed_unit(perm, inv, cur_g, K, u, &un, rot);
+  __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8));     // vmcnt(0): nothing outstanding later
+  for (int i = 0; i < n; ++i) {
+    wait_vmcnt_lgkm0<63>();                        // this wave's LDS reads of pass i-1
+    __builtin_amdgcn_s_barrier();
+    const int r = r0 + i * rpp + ro;
+    if (ro < rpp && r < r1) {                      // quad-uniform: units is a multiple of 4
+      if (kGrouped) {
+        const int g = gc.at(offsets, G, r);
+        if (g != cur_g) {
+          load_packed_unit(perm, inv, g, K, u, &un, rot);
+          __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8));
+          cur_g = g;
+        }
+      }
+      const uint16_t* row = reinterpret_cast<const uint16_t*>(stg + (i % kNS) * kShortStage) + ro * K;
+      float z[8];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint32_t sp = un.src2[e];
+        z[2 * e] = __uint_as_float(static_cast<uint32_t>(row[sp & 0xFFFFu]) << 16) * un.d[2 * e];
+        z[2 * e + 1] = __uint_as_float(static_cast<uint32_t>(row[sp >> 16]) << 16) * un.d[2 * e + 1];
+      }
+      if constexpr (kPacked) {
+        const PackedSink psink(Aq, Asc, r, steps, sgroups);
+        pad_row_tail(psink, u, units, nb, steps, sgroups);
+        quantize_store(z, u, tail_unit0, k_tail >> 3, k_tail >> 5, psink, rs);
+      } else {
+        quantize_store(z, u, tail_unit0, k_tail >> 3, k_tail >> 5,
+                       RowSink{Aq + static_cast<int64_t>(r) * row_bytes, Asc + static_cast<int64_t>(r) * nb},
+                       rs);
+      }
+    }
+  }
+  // Packed layout: the rows of the last 16-row block past M, one to a workgroup.
+  if constexpr (kPacked) {
+    for (int r = M + static_cast<int>(blockIdx.x); r < ((M + 15) & ~15); r += static_cast<int>(gridDim.x)) {
+      const PackedSink psink(Aq, Asc, r, steps, sgroups);
+      for (int v = tid; v < steps * 16; v += kComputeThreads) psink.word(v, 0u);
+      for (int b = tid; b < sgroups * 16; b += kComputeThreads) psink.scale(b, 127u);
+    }
+  }
+}
+
+// From this many channels in all on; below, the copies' start costs more than the
+// waits (us, here / act_quant_lds_kernel, row-major: 8192 x 768 6.6 / 7.0, 4096 x 768
+// 4.9 / 4.9, 2048 x 768 4.3 / 3.7, 4096 x 1440 in groups 8.2 / 8.8, 2048 x 1440 6.3 /
+// 6.2, 16384 x 256 5.1 / 5.2).
+bool short_rows(int M, int K) { return static_cast<int64_t>(M) * K >= 5500000; }
+
+template <bool kGrouped, bool kPacked>
+hipError_t launch_short(const uint16_t* X, int64_t ld_x, int M, int K, int k_tail, const float* inv,
+                        const int32_t* perm, const int32_t* offsets, int G, uint8_t* Aq, uint8_t* Asc,
+                        int num_cus, hipStream_t stream) {
+  const int rows_per_wg = lds_rows_per_wg(M, K >> 3, num_cus);
+  act_quant_short_kernel<kGrouped, kPacked><<<(M + rows_per_wg - 1) / rows_per_wg, kDmaThreads, 0, stream>>>(
+      X, ld_x, M, K, k_tail, inv, perm, offsets, G, rows_per_wg, Aq, Asc);
+  return hipGetLastError();
+}
+
+template <bool kGrouped, int kUnits, bool kPacked = false>
+void launch_lds(dim3 grid, size_t lds, hipStream_t stream, const uint16_t* X, int64_t ld_x,
+                int M, int K, int k_tail, const float* inv, const int32_t* perm,
+                const int32_t* offsets, int G, int rows_per_wg, uint8_t* Aq, uint8_t* Asc) {
+  act_quant_lds_kernel<kGrouped, kUnits, kPacked><<<grid, kLdsThreads, lds, stream>>>(
+      X, ld_x, M, K, k_tail, inv, perm, offsets, G, rows_per_wg, Aq, Asc);
 }
 
 // Stage classes of the copy kernel by row length (2K bytes): stage bytes, stages,
@@ -806,6 +941,13 @@ hipError_t launch_act_quant_kernel(const uint16_t* X, int64_t ld_x, int M, int K
     return launch_dma<false, false>(X, ld_x, M, K, k_tail, inv_scale_pos, perm, nullptr, 1, Aq, Asc,
                                     num_cus, stream);
   }
+  if (kernel == 5 || (kernel == 0 && short_rows(M, K))) {
+    if (grouped)
+      return launch_short<true, false>(X, ld_x, M, K, k_tail, inv_scale_pos, perm, goff, G, Aq, Asc,
+                                       num_cus, stream);
+    return launch_short<false, false>(X, ld_x, M, K, k_tail, inv_scale_pos, perm, nullptr, 1, Aq, Asc,
+                                      num_cus, stream);
+  }
   // At most 2 * 2048 * 16 bytes = 64 KiB of LDS: within the default limit.
   const size_t lds = lds_kernel_bytes(K);
   const int per_thread = (units + kLdsThreads - 1) / kLdsThreads;   // 1..4 (K <= 16384)
@@ -860,6 +1002,13 @@ hipError_t launch_act_quant_packed_kernel(const uint16_t* X, int64_t ld_x, int M
                                     num_cus, stream, window);
     return launch_dma<false, true>(X, ld_x, M, K, k_tail, inv_scale_pos, perm, nullptr, 1, Ap, Aps,
                                    num_cus, stream, window);
+  }
+  if (kernel == 5 || (kernel == 0 && short_rows(M, K))) {
+    if (grouped)
+      return launch_short<true, true>(X, ld_x, M, K, k_tail, inv_scale_pos, perm, off, G, Ap, Aps,
+                                      num_cus, stream);
+    return launch_short<false, true>(X, ld_x, M, K, k_tail, inv_scale_pos, perm, nullptr, 1, Ap, Aps,
+                                     num_cus, stream);
   }
   const int units = K >> 3;
   const size_t lds = lds_kernel_bytes(K);

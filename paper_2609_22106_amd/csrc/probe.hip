@@ -275,7 +275,8 @@ int prq_probe_mfma32(const void* a, const void* b, const void* sa, const void* s
 int prq_tune_act_quant(const void* X, int64_t ld_x, int M, int K, int k_tail, const float* inv,
                        const int32_t* perm, uint8_t* Aq, uint8_t* Asc, int kernel,
                        hipStream_t stream) {
-  if (M <= 0 || K <= 0 || K % 32 || k_tail % 32 || k_tail > K || K > 16384 || ld_x < K) return -1;
+  if (M <= 0 || K <= 0 || K % 32 || k_tail % 32 || k_tail > K || K > 16384 || ld_x < K || (kernel == 5 && K >= 2048))
+    return -1;
   return prq::launch_act_quant_kernel(static_cast<const uint16_t*>(X), ld_x, M, K, k_tail, inv, perm,
                                       nullptr, 1, Aq, Asc, 256, kernel, stream) == hipSuccess
              ? 0
@@ -285,13 +286,14 @@ int prq_tune_act_quant(const void* X, int64_t ld_x, int M, int K, int k_tail, co
 // The same into the packed activation layout (0 automatic, 1 one row per workgroup row,
 // 2 register-staged, 3 LDS stages
 // with the output through an LDS window where it fits, 4 LDS stages with the
-// output stored directly), its workgroups sized for num_cus CUs.
+// output stored directly, 5 short rows copied a pass at a time, K < 2048), its
+// workgroups sized for num_cus CUs.
 int prq_tune_act_quant_packed(const void* X, int64_t ld_x, int M, int K, int k_tail,
                               const float* inv, const int32_t* perm, const int32_t* off, int G,
                               uint8_t* Ap, uint8_t* Aps, int kernel, int num_cus,
                               hipStream_t stream) {
   if (M <= 0 || K <= 0 || K % 32 || k_tail % 32 || k_tail > K || K > 16384 || ld_x < K ||
-      kernel < 0 || kernel > 4 || num_cus <= 0)
+      kernel < 0 || kernel > 5 || (kernel == 5 && K >= 2048) || num_cus <= 0)
     return -1;
   return prq::launch_act_quant_packed_kernel(static_cast<const uint16_t*>(X), ld_x, M, K, k_tail,
                                              inv, perm, off, G, Ap, Aps, num_cus, kernel,

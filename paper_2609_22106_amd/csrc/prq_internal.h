@@ -53,7 +53,8 @@ hipError_t launch_act_quant(const uint16_t* X, int64_t ld_x, int M, int K, int k
                             const int32_t* group_offsets, int G, uint8_t* Aq, uint8_t* Asc,
                             int num_cus, hipStream_t stream);
 // kernel: 0 = by row count, 1 = the few-rows kernel, 2 = the many-rows kernel with
-// register-staged rows, 3 = the many-rows kernel with rows copied into LDS stages.
+// register-staged rows, 3 = the many-rows kernel with rows copied into LDS stages,
+// 5 = the same for several short rows a stage (K < 2048).
 hipError_t launch_act_quant_kernel(const uint16_t* X, int64_t ld_x, int M, int K, int k_tail,
                                    const float* inv_scale, const int32_t* perm,
                                    const int32_t* group_offsets, int G, uint8_t* Aq, uint8_t* Asc,
@@ -68,7 +69,8 @@ hipError_t launch_act_quant_packed(const uint16_t* X, int64_t ld_x, int M, int K
                                    int num_cus, hipStream_t stream);
 // kernel: 0 = automatic, 2 = register-staged rows, 3 = rows copied into LDS stages
 // with the output through an 8-row LDS window wherever it fits (automatic: only
-// where it pays), 4 = as 3 with the output stored directly.
+// where it pays), 4 = as 3 with the output stored directly, 5 = several short rows a
+// stage (K < 2048).
 hipError_t launch_act_quant_packed_kernel(const uint16_t* X, int64_t ld_x, int M, int K,
                                           int k_tail, const float* inv_scale_pos,
                                           const int32_t* perm, const int32_t* group_offsets,

@@ -250,3 +250,50 @@ def test_kernel_choice_padding_and_group_search(K, k, M, G):
     ep, es = pack_rows(rq, rs)
     np.testing.assert_array_equal(host(out.Aps), es)
     np.testing.assert_array_equal(host(out.Ap), ep)
+
+
+# (K, k, M, G, ld): the copies of several short rows a stage: one unit a row, a
+# stage not filled by whole rows, the longest row; rows of the last pass missing;
+# strided rows; groups changing inside a pass.
+SHORT = [(32, 32, 700, 1, 32), (768, 64, 333, 1, 768), (768, 64, 331, 7, 776), (1440, 96, 258, 1, 1472),
+         (1440, 0, 200, 90, 1440), (2016, 32, 130, 3, 2016)]
+
+
+@pytest.mark.parametrize("K,k,M,G,ld", SHORT)
+def test_short_row_copy_kernel(K, k, M, G, ld):
+    """act_quant_short_kernel forced (the tuning entry; AUTO takes it for larger
+    calls): row-major where ungrouped, and packed."""
+    import ctypes
+    from paper_2609_22106_amd import build, prq
+    from tests.packing import pack_rows
+    rng = np.random.default_rng(K + M + G)
+    X = inputs.f32_to_bf16_bits((rng.standard_normal((M, ld)) * 3).astype(np.float32))
+    perm = np.stack([rng.permutation(K) for _ in range(G)]).astype(np.int32)
+    inv = rng.uniform(0.1, 4.0, (G, K)).astype(np.float32)
+    off = inputs.routed_offsets(np.bincount(rng.integers(0, G, M), minlength=G))
+    rq, rs = pq.quant_act_grouped(X[:, :K], inv, perm, off, k)
+    lib = ctypes.CDLL(build.PROBE_LIB)
+    P, I, L = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64
+    lib.prq_tune_act_quant.argtypes = [P, L, I, I, I, P, P, P, P, I, P]
+    lib.prq_tune_act_quant_packed.argtypes = [P, L, I, I, I, P, P, P, I, P, P, I, I, P]
+    dX, di, dp, do = dev(X), dev(_pos(inv, perm)), dev(perm), dev(off)
+    stream = torch.cuda.current_stream().cuda_stream
+    say("short rows case:", K, k, M, G, ld)
+    cb, sb = prq.prq_packed_act_bytes(M, K + k)
+    Ap = torch.full((cb,), 0x5A, dtype=torch.uint8, device="cuda")
+    Aps = torch.full((sb,), 0xA5, dtype=torch.uint8, device="cuda")
+    assert lib.prq_tune_act_quant_packed(dX.data_ptr(), ld, M, K, k, di.data_ptr(), dp.data_ptr(),
+                                         do.data_ptr() if G > 1 else None, G, Ap.data_ptr(),
+                                         Aps.data_ptr(), 5, 7, stream) == 0
+    torch.cuda.synchronize()
+    ep, es = pack_rows(rq, rs)
+    np.testing.assert_array_equal(host(Aps), es)
+    np.testing.assert_array_equal(host(Ap), ep)
+    if G == 1:
+        Aq = torch.empty((M, (K + k) // 2), dtype=torch.uint8, device="cuda")
+        Asc = torch.empty((M, (K + k) // 32), dtype=torch.uint8, device="cuda")
+        assert lib.prq_tune_act_quant(dX.data_ptr(), ld, M, K, k, di.data_ptr(), dp.data_ptr(),
+                                      Aq.data_ptr(), Asc.data_ptr(), 5, stream) == 0
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(host(Asc), rs)
+        np.testing.assert_array_equal(host(Aq), rq)

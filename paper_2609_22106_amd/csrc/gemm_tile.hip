@@ -161,7 +161,7 @@ struct TileStage {
   static constexpr int kABlk = kBM / 16, kBBlk = kBN / 16;
   static constexpr int kOffB = kABlk * 1024;
   static constexpr int kOffAs = (kABlk + kBBlk) * 1024;
-  static constexpr int kAsBytes = kAMode == kAPacked ? kABlk * 256 : 0;
+  static constexpr int kAsBytes = kAMode == kAPacked ? (kABlk + 3) / 4 * 1024 : 0;
   static constexpr int kOffBs = kOffAs + kAsBytes;
   static constexpr int kBytes = kOffBs + kBBlk * 256;
 };
@@ -629,10 +629,12 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_grouped_persist_kernel(
   constexpr int kFM = kTM / 32, kFN = kTN / 32;
   static_assert(kTM % 32 == 0 && kTN % 32 == 0, "wave tile of whole 32x32 fragments");
   constexpr int kABlk = L::kABlk, kBBlk = L::kBBlk;
-  static_assert(kABlk % kWaves == 0 && kBBlk % kWaves == 0, "code blocks split evenly over waves");
-  static_assert(kABlk % 4 == 0 && kBBlk % 4 == 0, "scales move four block entries per instruction");
-  constexpr int kAPer = kABlk / kWaves, kBPer = kBBlk / kWaves;
-  constexpr int kAsChunks = kABlk / 4, kBsChunks = kBBlk / 4;
+  static_assert(kBBlk % kWaves == 0, "feature blocks split evenly over waves");
+  static_assert(kBBlk % 4 == 0, "scales move four block entries per instruction");
+  // Row blocks that do not divide over the waves: the last one is loaded again
+  // into its own place; scale chunks are whole (entries past the tile unused).
+  constexpr int kAPer = (kABlk + kWaves - 1) / kWaves, kBPer = kBBlk / kWaves;
+  constexpr int kAsChunks = (kABlk + 3) / 4, kBsChunks = kBBlk / 4;
   constexpr int kScChunks = kAsChunks + kBsChunks;   // one list dealt to the waves
   constexpr int kScPer = (kScChunks + kWaves - 1) / kWaves;
   constexpr int kLoads = kAPer + kBPer + kScPer;
@@ -717,7 +719,7 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_grouped_persist_kernel(
     Offs o;
 #pragma unroll
     for (int i = 0; i < kAPer; ++i) {
-      const int rb = min((t.row_begin >> 4) + wave + i * kWaves, nblk - 1);
+      const int rb = min((t.row_begin >> 4) + min(wave + i * kWaves, kABlk - 1), nblk - 1);
       o.a[i] = static_cast<uint32_t>(rb) * steps * 1024 + lane * 16;
     }
 #pragma unroll
@@ -751,7 +753,7 @@ __global__ __launch_bounds__(kWM * kWN * 64) void gemm_grouped_persist_kernel(
 #pragma unroll
     for (int i = 0; i < kAPer; ++i)
       __builtin_amdgcn_global_load_lds(PRQ_GPTR(Ap + ((use_next ? on.a[i] : oc.a[i]) + s * 1024u)),
-                                       PRQ_LPTR(st + (wave + i * kWaves) * 1024), 16, 0, 0);
+                                       PRQ_LPTR(st + min(wave + i * kWaves, kABlk - 1) * 1024), 16, 0, 0);
 #pragma unroll
     for (int i = 0; i < kBPer; ++i)
       __builtin_amdgcn_global_load_lds(PRQ_GPTR(W + ((use_next ? on.b[i] : oc.b[i]) + s * 1024u)),
@@ -1180,19 +1182,16 @@ hipError_t launch_gemm_tile_packed(const uint8_t* Ap, const uint8_t* Aps, int M,
                        stream);
 }
 
-// The persistent grouped kernel (128 x 128 tiles) over num_cus CUs: as many
-// workgroups as fit on them at once, a multiple of the XCD count.
-hipError_t launch_grouped_persist(const uint8_t* Ap, const uint8_t* Aps, int M,
-                                  const int32_t* off, int E, const uint8_t* Wp,
-                                  const uint8_t* Wps, int N, int K_aug, float* Y, int num_cus,
-                                  hipStream_t stream) {
-  const int64_t steps = (K_aug + kStepK - 1) / kStepK;
-  if (!off || E < 1 || E > 64 * kXcds || num_cus < 1 ||
-      static_cast<int64_t>((M + 15) / 16) * steps * 1024 >= (int64_t{1} << 31) ||
-      static_cast<int64_t>(N / 16) * steps * 1024 >= (int64_t{1} << 31))
-    return hipErrorInvalidValue;
-  constexpr int kThreads = 256;
-  auto kernel = gemm_grouped_persist_kernel<128, 128, 2, 2, 4>;
+namespace {
+
+// The persistent grouped kernel over num_cus CUs: as many workgroups as fit on
+// them at once, a multiple of the XCD count.
+template <int kBM, int kBN, int kWM, int kWN>
+hipError_t launch_persist_shape(const uint8_t* Ap, const uint8_t* Aps, int M, const int32_t* off, int E,
+                                const uint8_t* Wp, const uint8_t* Wps, int N, int K_aug, float* Y,
+                                int num_cus, hipStream_t stream) {
+  constexpr int kThreads = kWM * kWN * 64;
+  auto kernel = gemm_grouped_persist_kernel<kBM, kBN, kWM, kWN, 4>;
   static int per_cu = 0;   // the kernel's occupancy (gfx950 only: the same on every device)
   if (per_cu == 0) {
     int n = 0;
@@ -1205,23 +1204,58 @@ hipError_t launch_grouped_persist(const uint8_t* Ap, const uint8_t* Aps, int M,
   return hipGetLastError();
 }
 
-// Shape of the grouped packed GEMM.  128 x 128 throughout: on the expert
-// shape (~256 rows per expert, N = 2048, K + k = 832) it measured 158 us
-// against 167 (256 x 256) and 220 (256 x 128), and smaller row tiles waste
-// less on experts with fewer rows.
-int choose_grouped_packed_shape(int rows_per_expert, int N, int K_aug, int E) {
-  (void)rows_per_expert;
-  (void)N;
-  (void)K_aug;
-  return E <= 64 * kXcds ? kShapePersist : 2;
+// Mean row tiles of `bm` rows per expert for `rows` routed rows on average, the
+// counts spread as independent routing spreads them (standard deviation
+// sqrt(rows)) and an expert's first row anywhere in its 16-row block.
+double mean_row_tiles(double rows, int bm) {
+  static const double kZ[] = {-1.6, -0.8, 0.0, 0.8, 1.6}, kWeight[] = {0.115, 0.235, 0.3, 0.235, 0.115};
+  double mean = 0.0;
+  for (int lead = 1; lead < 16; lead += 2)
+    for (int z = 0; z < 5; ++z)
+      mean += kWeight[z] / 8.0 * std::ceil(std::max(1.0, rows + kZ[z] * std::sqrt(rows) + lead) / bm);
+  return mean;
+}
+
+}  // namespace
+
+hipError_t launch_grouped_persist(const uint8_t* Ap, const uint8_t* Aps, int M,
+                                  const int32_t* off, int E, const uint8_t* Wp,
+                                  const uint8_t* Wps, int N, int K_aug, float* Y, int shape,
+                                  int num_cus, hipStream_t stream) {
+  const int64_t steps = (K_aug + kStepK - 1) / kStepK;
+  if (!off || E < 1 || E > 64 * kXcds || num_cus < 1 ||
+      static_cast<int64_t>((M + 15) / 16) * steps * 1024 >= (int64_t{1} << 31) ||
+      static_cast<int64_t>(N / 16) * steps * 1024 >= (int64_t{1} << 31))
+    return hipErrorInvalidValue;
+  if (shape == kShapePersistWide)
+    return launch_persist_shape<160, 256, 1, 8>(Ap, Aps, M, off, E, Wp, Wps, N, K_aug, Y, num_cus, stream);
+  return launch_persist_shape<128, 128, 2, 2>(Ap, Aps, M, off, E, Wp, Wps, N, K_aug, Y, num_cus, stream);
+}
+
+// Shape of the grouped packed GEMM: the persistent kernel where a wave's lanes hold
+// an XCD's experts, with the tile that computes fewer rows for nothing.  256 routed
+// rows and a lead of up to 15 make three 128-row tiles of most experts but two of
+// 160.  Wide (160 x 256, eight waves) against 128 x 128 (two workgroups per CU of
+// four waves), us, E = 128: rows per expert 256, N = 2048, K + k = 832 104.3 / 120.7;
+// 128 rows 59.8 / 71.1; 256 rows of 1040 x 1536 71.2 / 80.5; 187 rows of 1536 x
+// 1056 81.1 / 76.3; 64 rows 48.4 / 43.1; 37 rows 46.0 / 39.3: wide where its rows at
+// 0.93 of the time each are fewer.  (160 x 128 with three stages 123.6, 192 x 128
+// 151.8; 96 x 128 118.3, and 40.4 at 64 rows.  One workgroup per tile: 158 with 128 x
+// 128, 167 with 256 x 256, 220 with 256 x 128 before the persistent kernel's 119.)
+int choose_grouped_packed_shape(int M_total, int N, int E) {
+  if (E > 64 * kXcds) return 2;
+  const double rows = static_cast<double>(M_total) / E;
+  const double wide = 0.93 * 160 * mean_row_tiles(rows, 160) * ((N + 255) / 256 * 256);
+  const double narrow = 128 * mean_row_tiles(rows, 128) * ((N + 127) / 128 * 128);
+  return wide < narrow ? kShapePersistWide : kShapePersist;
 }
 
 hipError_t launch_grouped_gemm_tile_packed(const uint8_t* Ap, const uint8_t* Aps, int M_total,
                                            const int32_t* group_offsets, int E, const uint8_t* Wp,
                                            const uint8_t* Wps, int N, int K_aug, float* Y,
                                            int shape, int num_cus, hipStream_t stream) {
-  if (shape == kShapePersist)
-    return launch_grouped_persist(Ap, Aps, M_total, group_offsets, E, Wp, Wps, N, K_aug, Y,
+  if (shape == kShapePersist || shape == kShapePersistWide)
+    return launch_grouped_persist(Ap, Aps, M_total, group_offsets, E, Wp, Wps, N, K_aug, Y, shape,
                                   num_cus, stream);
   return launch_region(Ap, Aps, M_total, group_offsets, E, Wp, Wps, N, K_aug, Y, shape, true, 0,
                        N / 16, stream);

@@ -411,13 +411,14 @@ int prq_tune_gemm_tile_split(const uint8_t* A, const uint8_t* As, int M, const u
 }
 
 // The grouped tile GEMM on a packed activation with a forced shape (0-3: a
-// workgroup per tile; 4: the persistent kernel over num_cus CUs).
+// workgroup per tile; 4, 5: the persistent kernel, 128 x 128 and 160 x 256 tiles,
+// over num_cus CUs).
 int prq_tune_grouped_gemm_tile_packed(const uint8_t* Ap, const uint8_t* Aps, int M,
                                       const int32_t* off, int E, const uint8_t* Wp,
                                       const uint8_t* Wps, int N, int K_aug, float* Y, int shape,
                                       int num_cus, hipStream_t stream) {
-  if (shape < 0 || shape > prq::kShapePersist || N % 16 || K_aug % 32 || M <= 0 || E < 1 ||
-      !off || num_cus < 0 || (shape == prq::kShapePersist && (num_cus < 1 || E > 512)))
+  if (shape < 0 || shape > prq::kShapePersistWide || N % 16 || K_aug % 32 || M <= 0 || E < 1 ||
+      !off || num_cus < 0 || (shape >= prq::kShapePersist && (num_cus < 1 || E > 512)))
     return -1;
   return prq::launch_grouped_gemm_tile_packed(Ap, Aps, M, off, E, Wp, Wps, N, K_aug, Y, shape,
                                               num_cus, stream) == hipSuccess

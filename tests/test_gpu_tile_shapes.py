@@ -168,3 +168,42 @@ def test_planned_call_equals_forced_shape(packed, M, N, K_aug):
     torch.cuda.synchronize()
     assert not torch.isnan(want).any()
     assert torch.equal(want, got)
+
+
+# (counts, N, K_aug, CUs): experts of exactly a wide tile's 160 rows, one more and
+# one fewer, of a row, empty first and last; tiles cut by the lead of a shared
+# 16-row block; N below, at and past the 256 columns; steps below and past the four
+# stages; fewer workgroups than tiles (8 CUs) and more.
+WIDE = [([0, 160, 161, 159, 1, 0], 256, 832, 8), ([3, 157, 320, 5, 330], 240, 544, 256),
+        ([17, 0, 0, 500, 31, 16, 144, 176, 20, 40], 528, 416, 8), ([1], 16, 32, 256),
+        ([40] * 70, 272, 1056, 16)]
+
+
+@pytest.mark.parametrize("counts,N,K_aug,cus", WIDE)
+def test_wide_persistent_grouped(counts, N, K_aug, cus):
+    """The persistent grouped kernel's 160 x 256 tiles: the bits of its 128 x 128
+    tiles (both add a row's products in K order) and the oracle's product."""
+    from paper_2609_22106_amd import build, prq
+    from tests.packing import pack_rows
+    rng = np.random.default_rng(sum(counts) + N)
+    E, M = len(counts), sum(counts)
+    off = inputs.routed_offsets(counts)
+    Aq, Asc = inputs.random_mxfp4(rng, M, K_aug)
+    Wq, Wsc = inputs.random_mxfp4(rng, (E, N), K_aug)
+    W = prq.prq_pack_weight(dev(Wq), dev(Wsc))
+    A, As = map(dev, pack_rows(Aq, Asc))
+    do = dev(off)
+    lib = ctypes.CDLL(build.PROBE_LIB)
+    P, I = ctypes.c_void_p, ctypes.c_int
+    lib.prq_tune_grouped_gemm_tile_packed.argtypes = [P, P, I, P, I, P, P, I, I, P, I, I, P]
+    out = []
+    for shape in (4, 5):
+        Y = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+        say("wide grouped case:", shape, counts[:8], N, K_aug, cus)
+        assert lib.prq_tune_grouped_gemm_tile_packed(
+            A.data_ptr(), As.data_ptr(), M, do.data_ptr(), E, W.Wp.data_ptr(), W.Wps.data_ptr(), N,
+            K_aug, Y.data_ptr(), shape, cus, torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        out.append(host(Y))
+    np.testing.assert_array_equal(out[0].view(np.uint32), out[1].view(np.uint32))
+    assert_gemm_close(out[1], pq.grouped_gemm(Aq, Asc, off, Wq, Wsc), f"wide {N}x{K_aug}")

@@ -136,6 +136,24 @@ def _stream_of_call(stream):
     return _stream(stream)
 
 
+def _alloc(make, shape, dtype, device, stream, kept=True):
+    """make(shape) for a call on `stream`, which may not be the current one: made
+    under that stream, so that the call is ordered after a fill and after the last
+    use of memory that another tensor gave back.  kept: a tensor that the caller
+    gets and uses on the current stream too (it holds its memory until that is done)."""
+    device = torch.device(device)
+    if stream is None or device.type != "cuda":
+        return make(shape, dtype=dtype, device=device)
+    if not isinstance(stream, torch.cuda.Stream):
+        stream = torch.cuda.ExternalStream(stream.cuda_stream, device=device)
+    with torch.cuda.stream(stream):
+        t = make(shape, dtype=dtype, device=device)
+    current = torch.cuda.current_stream(device)
+    if kept and current != stream:
+        t.record_stream(current)
+    return t
+
+
 # --------------------------------------------------------------- prepare ---
 def prq_prepare(W_bf16, Xcal_bf16, alpha, k_tail, scale_mode="smooth", with_col_err=False,
                 scale_search=False):
@@ -324,9 +342,9 @@ def prq_quant_act(X, K, k_tail, inv_scale_pos=None, perm=None, group_offsets=Non
         raise ValueError(f"X rows must hold K={K} contiguous values (shape {tuple(X.shape)}, "
                          f"strides {X.stride()})")
     if Aq is None:
-        Aq = torch.empty((M, K_aug // 2), dtype=torch.uint8, device=X.device)
+        Aq = _alloc(torch.empty, (M, K_aug // 2), torch.uint8, X.device, stream)
     if Asc is None:
-        Asc = torch.empty((M, K_aug // 32), dtype=torch.uint8, device=X.device)
+        Asc = _alloc(torch.empty, (M, K_aug // 32), torch.uint8, X.device, stream)
     if not (X.is_cuda and _is(Aq, _U8, (M, K_aug // 2)) and _is(Asc, _U8, (M, K_aug // 32))
             and _scales_fit(inv_scale_pos, perm, group_offsets, G, K)):
         _need(Aq, "Aq", torch.uint8, (M, K_aug // 2))
@@ -382,8 +400,8 @@ def prq_pack_weight(Wq, Wsc, stream=None):
     _need(Wsc, "Wsc", torch.uint8, tuple(Wq.shape[:-1]) + (K_aug // 32,))
     _on_gpu(Wq=Wq, Wsc=Wsc)
     cb, sb = prq_packed_weight_bytes(E, N, K_aug)
-    Wp = torch.empty(cb, dtype=torch.uint8, device=Wq.device)
-    Wps = torch.empty(sb, dtype=torch.uint8, device=Wq.device)
+    Wp = _alloc(torch.empty, cb, torch.uint8, Wq.device, stream)
+    Wps = _alloc(torch.empty, sb, torch.uint8, Wq.device, stream)
     _check(_pack(_ptr(Wq), _ptr(Wsc), E, N, K_aug, _ptr(Wp), _ptr(Wps), _stream(stream)),
            "prq_pack_weight")
     return PackedWeight(Wp, Wps, E, N, K_aug)
@@ -401,12 +419,12 @@ def prq_gemm(Aq, Asc, W, Y=None, workspace=None, variant=GEMM_AUTO, splits=0, st
     if W.E != 1:
         raise ValueError("prq_gemm takes a single weight (E = 1); use prq_grouped_gemm")
     if Y is None:
-        Y = torch.empty((M, N), dtype=torch.float32, device=W.Wp.device)
+        Y = _alloc(torch.empty, (M, N), torch.float32, W.Wp.device, stream)
     _check_gemm_operands(Aq, Asc, W, Y, M)
     if workspace is None:
         need = prq_gemm_workspace_bytes(M, N, K_aug, variant, splits)
         if need:
-            workspace = torch.zeros(need, dtype=torch.uint8, device=W.Wp.device)
+            workspace = _alloc(torch.zeros, need, torch.uint8, W.Wp.device, stream, kept=False)
     ws, ws_bytes = _workspace_arg(workspace)
     st = _gemm_ex(Aq.data_ptr(), Asc.data_ptr(), M, W.Wp.data_ptr(), W.Wps.data_ptr(), N, K_aug,
                   Y.data_ptr(), ws, ws_bytes, variant, splits, _stream_of_call(stream))
@@ -464,8 +482,8 @@ def prq_quant_act_packed(X, K, k_tail, inv_scale_pos=None, perm=None, out=None, 
                          f"strides {X.stride()})")
     if out is None:
         cb, sb = prq_packed_act_bytes(M, K_aug)
-        out = PackedAct(torch.empty(cb, dtype=torch.uint8, device=X.device),
-                        torch.empty(sb, dtype=torch.uint8, device=X.device), M, K_aug)
+        out = PackedAct(_alloc(torch.empty, cb, torch.uint8, X.device, stream),
+                        _alloc(torch.empty, sb, torch.uint8, X.device, stream), M, K_aug)
     if out.M != M or out.K_aug != K_aug:
         raise ValueError(f"out holds {out.M} rows of K_aug {out.K_aug}, expected {M} x {K_aug}")
     if not (X.is_cuda and _packed_act_fits(out) and _scales_fit(inv_scale_pos, perm, group_offsets, G, K)):
@@ -499,8 +517,8 @@ def prq_swiglu_quant(gate, up, K_aug, packed=False, out=None, stream=None):
     if packed:
         if out is None:
             cb, sb = prq_packed_act_bytes(M, K_aug)
-            out = PackedAct(torch.empty(cb, dtype=torch.uint8, device=gate.device),
-                            torch.empty(sb, dtype=torch.uint8, device=gate.device), M, K_aug)
+            out = PackedAct(_alloc(torch.empty, cb, torch.uint8, gate.device, stream),
+                            _alloc(torch.empty, sb, torch.uint8, gate.device, stream), M, K_aug)
         if out.M != M or out.K_aug != K_aug:
             raise ValueError(f"out holds {out.M} rows of K_aug {out.K_aug}, expected {M} x {K_aug}")
         if not _packed_act_fits(out):
@@ -508,8 +526,8 @@ def prq_swiglu_quant(gate, up, K_aug, packed=False, out=None, stream=None):
         A, As = out.Ap, out.Aps
     else:
         if out is None:
-            out = (torch.empty((M, K_aug // 2), dtype=torch.uint8, device=gate.device),
-                   torch.empty((M, K_aug // 32), dtype=torch.uint8, device=gate.device))
+            out = (_alloc(torch.empty, (M, K_aug // 2), torch.uint8, gate.device, stream),
+                   _alloc(torch.empty, (M, K_aug // 32), torch.uint8, gate.device, stream))
         A, As = out
         if not (_is(A, _U8, (M, K_aug // 2)) and _is(As, _U8, (M, K_aug // 32))):
             _need(A, "Aq", torch.uint8, (M, K_aug // 2))
@@ -535,7 +553,7 @@ def prq_gemm_packed(A, W, Y=None, workspace=None, stream=None):
         raise ValueError(f"K_aug differs: activation {A.K_aug}, weight {W.K_aug}")
     M, N = A.M, W.N
     if Y is None:
-        Y = torch.empty((M, N), dtype=torch.float32, device=W.Wp.device)
+        Y = _alloc(torch.empty, (M, N), torch.float32, W.Wp.device, stream)
     if not (_is(Y, _F32, (M, N)) and _packed_act_fits(A) and _weight_fits(W)):
         _need(Y, "Y", torch.float32, (M, N))
         A.check_sizes()
@@ -555,7 +573,7 @@ def prq_grouped_gemm_packed(A, group_offsets, W, Y=None, stream=None):
         raise ValueError(f"K_aug differs: activation {A.K_aug}, weight {W.K_aug}")
     M, E, N = A.M, W.E, W.N
     if Y is None:
-        Y = torch.empty((M, N), dtype=torch.float32, device=W.Wp.device)
+        Y = _alloc(torch.empty, (M, N), torch.float32, W.Wp.device, stream)
     if not (_is(Y, _F32, (M, N)) and _is(group_offsets, _I32, (E + 1,)) and _packed_act_fits(A)
             and _weight_fits(W)):
         _need(Y, "Y", torch.float32, (M, N))
@@ -579,7 +597,7 @@ def prq_grouped_gemm(Aq, Asc, group_offsets, W, Y=None, workspace=None, variant=
     M = Aq.shape[0]
     E, N, K_aug = W.E, W.N, W.K_aug
     if Y is None:
-        Y = torch.empty((M, N), dtype=torch.float32, device=W.Wp.device)
+        Y = _alloc(torch.empty, (M, N), torch.float32, W.Wp.device, stream)
     if not _is(group_offsets, _I32, (E + 1,)):
         _need(group_offsets, "group_offsets", torch.int32, (E + 1,))
     _check_gemm_operands(Aq, Asc, W, Y, M)

@@ -399,3 +399,63 @@ def test_workspace_rule_stays(M, N, K_aug, rows, packed):
     want = lambda r: HEAD + (r - 1) * M * N * 4 if r > 1 else 0  # noqa: E731
     assert prq.prq_gemm_workspace_bytes(M, N, K_aug) == want(rows)
     assert prq.prq_gemm_packed_workspace_bytes(M, N, K_aug) == want(packed)
+
+
+def test_a_calls_own_buffers_belong_to_its_stream(monkeypatch):
+    """Outputs and workspaces that a call makes for work on another stream than the
+    current one are allocated (and filled) under that stream, and outputs are known
+    to the current one: otherwise a workspace's fill, or the last use of memory given
+    back by another tensor, is not ordered before the call."""
+    import contextlib
+    from types import SimpleNamespace as NS
+
+    class Stream:
+        def __init__(self, handle):
+            self.cuda_stream = handle
+
+    now = [Stream(1)]
+    made, launched = [], []
+
+    @contextlib.contextmanager
+    def under(s):
+        now.append(s)
+        yield
+        now.pop()
+
+    class Buffer:
+        def __init__(self, kind, shape):
+            self.kind, self.made_on, self.recorded, self.M = kind, now[-1].cuda_stream, [], 0
+            self.shape = shape if isinstance(shape, tuple) else (shape,)
+            made.append(self)
+
+        def record_stream(self, s):
+            self.recorded.append(s.cuda_stream)
+
+        def data_ptr(self):
+            return 256
+
+        def numel(self):
+            return int(np.prod(self.shape))
+
+    class Dev:
+        type = "cuda"
+
+    torch_ = prq.torch
+    monkeypatch.setattr(torch_, "device", lambda d: d)
+    monkeypatch.setattr(torch_, "empty", lambda shape, **kw: Buffer("empty", shape))
+    monkeypatch.setattr(torch_, "zeros", lambda shape, **kw: Buffer("zeros", shape))
+    monkeypatch.setattr(torch_.cuda, "Stream", Stream)
+    monkeypatch.setattr(torch_.cuda, "stream", under)
+    monkeypatch.setattr(torch_.cuda, "current_stream", lambda *a: now[-1])
+    monkeypatch.setattr(prq, "_check_gemm_operands", lambda *a: None)
+    monkeypatch.setattr(prq, "_workspace_arg", lambda w: (w.data_ptr(), w.numel()) if w is not None else (None, 0))
+    monkeypatch.setattr(prq, "_gemm_ex", lambda *a: launched.append(a[-1].value) or 0)
+    W = NS(E=1, N=2560, K_aug=4192, Wp=NS(device=Dev(), data_ptr=lambda: 256), Wps=NS(data_ptr=lambda: 256))
+    A = NS(shape=(333, 2096), data_ptr=lambda: 256)
+    prq.prq_gemm(A, A, W, stream=Stream(7))
+    assert launched == [7]
+    assert [(b.kind, b.made_on, b.recorded) for b in made] == [("empty", 7, [1]), ("zeros", 7, [])]
+    # every other buffer that the binding makes comes the same way
+    import inspect
+    import re
+    assert not re.findall(r"torch\.(?:empty|zeros)\(", inspect.getsource(prq))

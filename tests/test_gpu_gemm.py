@@ -481,3 +481,32 @@ def test_grouped_row_major_scales_at_odd_alignment():
         r0, r1 = off[e], off[e + 1]
         if r1 > r0:
             assert_gemm_close(y[r0:r1], pq.gemm(Aq[r0:r1], Asc[r0:r1], Wq[e], Wsc[e]), f"expert {e}")
+
+
+def test_split_call_on_another_stream_with_its_own_buffers():
+    """A call planned in K ranges that makes its own output and workspace, on a
+    stream that is not the current one and does not wait for it: the current
+    stream is still busy when the call's kernels run, and its later work reuses
+    freed memory while they do."""
+    prq = _prq()
+    rng = np.random.default_rng(21)
+    M, N, K_aug = 333, 2560, 4192
+    assert prq.prq_gemm_workspace_bytes(M, N, K_aug) > 0
+    Aq, Asc = inputs.random_mxfp4(rng, M, K_aug)
+    Wq, Wsc = inputs.random_mxfp4(rng, N, K_aug)
+    A, S, W = dev(Aq), dev(Asc), _packed(Wq, Wsc)
+    want = host(prq.prq_gemm(A, S, W))
+    side = torch.cuda.Stream()
+    busy = torch.randn(4096, 4096, device="cuda")
+    torch.cuda.synchronize()
+    say("gemm case: own workspace on another stream")
+    for _ in range(4):
+        x = busy
+        for _ in range(8):
+            x = x @ busy * 1e-2
+        Y = prq.prq_gemm(A, S, W, stream=side)
+        torch.cuda.current_stream().wait_stream(side)
+        got = Y.clone()
+        del Y
+        torch.full((M, N), float("nan"), device="cuda")
+        np.testing.assert_array_equal(host(got), want)

@@ -266,7 +266,7 @@ __global__ __launch_bounds__(kRowsThreads) void act_quant_rows_kernel(
   // 3. Gather from LDS, quantize, store.
   for (int rr = 0; rr < n; ++rr) {
     const int r = r0 + rr;
-    if (kGrouped) {
+    if (kGrouped && rr > 0) {   // (the first row's: cur_g)
       const int g = gc.at(offsets, G, r);
       if (g != cur_g) {
         load_packed_unit(perm, inv, g, K, uc, &un, rot);
@@ -541,8 +541,8 @@ __global__ __launch_bounds__(kDmaThreads) void act_quant_dma_kernel(
     __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xF << 8));   // vmcnt(0)
     cur_g = g;
   };
-  dev::GroupCursor gc(kGrouped ? dev::wave_find_group(offsets, G, r0) : 0);
-  if (!copier) load_units(kGrouped ? gc.at(offsets, G, r0) : 0);
+  dev::GroupCursor gc(kGrouped && !copier ? dev::wave_find_group(offsets, G, r0) : 0);
+  if (!copier) load_units(gc.g);
 
   // Rows [lo, hi) of the window of rows [w0, w0 + 8) from LDS to the packed
   // layout (compute waves): 16-byte code pieces, consecutive threads on

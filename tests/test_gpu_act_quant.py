@@ -8,7 +8,7 @@ torch = pytest.importorskip("torch")
 from oracle import prquant as pq                       # noqa: E402
 from paper_2609_22106_amd import inputs                # noqa: E402
 from tests.golden import load_hand_blocks              # noqa: E402
-from tests.gpu_util import dev, host, say              # noqa: E402
+from tests.gpu_util import dev, host, replay_us, say              # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -250,6 +250,24 @@ def test_kernel_choice_padding_and_group_search(K, k, M, G):
     ep, es = pack_rows(rq, rs)
     np.testing.assert_array_equal(host(out.Aps), es)
     np.testing.assert_array_equal(host(out.Ap), ep)
+
+
+@pytest.mark.parametrize("packed", [False, True])
+def test_group_search_in_many_groups(packed):
+    """The most groups there can be cost about as much as one load's worth of them
+    (measured 1.07 times): the search does not look at all of them (3.5 to 4 times)."""
+    from paper_2609_22106_amd import prq
+    M, K, k = 64, 768, 64
+    X = torch.randn(M, K, device="cuda").bfloat16()
+    us = []
+    for G in (64, 4096):
+        off = dev(inputs.routed_offsets(np.bincount(np.arange(M) * (G // M), minlength=G)))
+        inv = torch.ones(G, K, device="cuda")
+        perm = torch.arange(K, dtype=torch.int32, device="cuda").repeat(G, 1)
+        call = prq.prq_quant_act_packed if packed else prq.prq_quant_act
+        us.append(replay_us(lambda: call(X, K, k, inv, perm, group_offsets=off, G=G)))
+    say("group search us:", packed, us)
+    assert us[1] < 1.8 * us[0]
 
 
 # (K, k, M, G, ld): the copies of several short rows a stage: one unit a row, a

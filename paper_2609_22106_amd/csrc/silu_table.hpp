@@ -45,7 +45,7 @@ constexpr uint32_t kSiluTableBase = 0x3300;
 constexpr uint32_t kSiluTableHalf = 4096;
 
 struct SiluTable {
-  float v[2 * kSiluTableHalf];
+  alignas(16) float v[2 * kSiluTableHalf];
 };
 
 // p 2^n in one rounding (two power-of-two products, the first of them exact).

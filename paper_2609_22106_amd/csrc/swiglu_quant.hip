@@ -88,9 +88,11 @@ __device__ __forceinline__ void gated8(const uint4& gv, const uint4& uv, const f
 
 // Copy the table into LDS (every thread; a barrier follows).
 __device__ __forceinline__ void fill_table(float* tab) {
+  constexpr int kVecs = sizeof(dev::SiluTable) / 16;
+  static_assert(alignof(dev::SiluTable) == 16 && kVecs % kThreads[1] == 0, "moved 16 bytes a thread at a time");
   const uint4* src = reinterpret_cast<const uint4*>(kSiluTable.v);
 #pragma unroll
-  for (int i = 0; i < static_cast<int>(sizeof(dev::SiluTable)) / 16 / kThreads[1]; ++i)
+  for (int i = 0; i < kVecs / kThreads[1]; ++i)
     reinterpret_cast<uint4*>(tab)[threadIdx.x + i * kThreads[1]] = src[threadIdx.x + i * kThreads[1]];
 }
 

@@ -39,6 +39,15 @@ __device__ __forceinline__ float silu_seq(float g) {
   return __fdiv_rn(g, 1.0f + e);
 }
 
+// The sequence's result for a gate outside the table: below 2^-25 e^-g rounds to 1,
+// from 2^7 on 1 + e^-g rounds to 1, from -2^7 down e^-g is infinite (-inf / inf is the
+// device's NaN of an invalid division); NaN stays NaN.
+__device__ __forceinline__ float silu_outside(float g) {
+#pragma clang fp contract(off)
+  const float scaled = g * (__builtin_fabsf(g) < 1.0f ? 0.5f : g > 0.0f ? 1.0f : 0.0f);
+  return g == -INFINITY ? __uint_as_float(0xFFC00000u) : scaled;
+}
+
 // The table: entry sign * 4096 + (magnitude bits - kSiluTableBase) for the bf16
 // gate with those bits, magnitude bits 0x3300 (2^-25) .. 0x42FF (just below 2^7).
 constexpr uint32_t kSiluTableBase = 0x3300;

@@ -10,10 +10,11 @@
 // by the vector units instead.  From kTableMinUnits on, SiLU is therefore
 // looked up: the 8192 gates whose SiLU is not one exact operation, tabulated by
 // the compiler (silu_table.hpp), are copied into each workgroup's LDS (32 KiB,
-// four workgroups of 512 threads per CU) and gathered; a thread whose gates are
-// not all inside the table runs the sequence for its eight.  Measured at M =
-// 8192, K_aug = 9984 (371 MB): packed 113 -> 75.5 us (4.9 TB/s; a plain copy of as
-// many bytes takes 73), row-major 99 -> 75.2.
+// four workgroups of 512 threads per CU) and gathered; a wave with a gate outside
+// the table selects between the entry and that operation.  Measured at M = 8192,
+// K_aug = 9984 (371 MB): packed 113 -> 75.6 us (4.9 TB/s; a plain copy of as many bytes
+// takes 73), row-major 99 -> 75.6; one gate in twenty zero 79.6 and 80.6, all zero 80.6
+// and 81.1 (107 to 118 when such a thread ran the sequence for its eight gates).
 //
 // A wave's task in the packed layout is one K step (128 elements) of a 16-row
 // block: 8 lanes read 128 contiguous bytes of a row, and the wave writes the
@@ -36,7 +37,7 @@ namespace {
 // Threads of a workgroup with the table, and without; passes of a wave's task.
 constexpr int kThreads[2] = {256, 512};
 constexpr int kPasses[2] = {1, 4};
-constexpr int kPerCu = 4;            // workgroups with tables a CU holds (2048 threads, 128 KiB)
+constexpr int kPerCu = 4;            // workgroups with tables a CU holds (2048 threads, 128 KiB; 64 registers)
 
 // Type that task numbers are divided in: 32 bits without the table (few tasks:
 // a 64-bit division there costs 0.1 us of a 2.4 us call).
@@ -53,26 +54,39 @@ __device__ __forceinline__ void gated8(const uint4& gv, const uint4& uv, const f
   const uint32_t gw[4] = {gv.x, gv.y, gv.z, gv.w};
   const uint32_t uw[4] = {uv.x, uv.y, uv.z, uv.w};
   float s[8];
-  bool looked_up = false;
   if constexpr (kTable) {
     uint32_t at[8], most = 0;   // byte offset of the magnitude in its half of the table
+    constexpr uint32_t kHalf = 4 * dev::kSiluTableHalf;
+    auto entry = [&](uint32_t offset, uint32_t sign) {
+      return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(tab) + (offset + sign * kHalf));
+    };
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const uint32_t mag = (j & 1) ? (gw[j >> 1] >> 16) & 0x7FFFu : gw[j >> 1] & 0x7FFFu;
       at[j] = 4 * mag - 4 * dev::kSiluTableBase;
       most = max(most, at[j]);
     }
-    looked_up = most < 4 * dev::kSiluTableHalf;
-    if (looked_up) {
+    if (__all(most < kHalf)) {   // (the whole wave's branches)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const uint32_t sign = (j & 1) ? gw[j >> 1] >> 31 : (gw[j >> 1] >> 15) & 1u;
-        s[j] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(tab) +
-                                               (at[j] + sign * 4 * dev::kSiluTableHalf));
+      for (int j = 0; j < 8; ++j) s[j] = entry(at[j], (j & 1) ? gw[j >> 1] >> 31 : (gw[j >> 1] >> 15) & 1u);
+    } else {
+      // Two gates at a time, from words that the compiler cannot take for those
+      // above: 64 registers hold four workgroups a CU.
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        uint32_t w = gw[j];
+        asm volatile("" : "+v"(w));
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const float g = __uint_as_float(h ? w & 0xFFFF0000u : w << 16);
+          const uint32_t offset = (__float_as_uint(fabsf(g)) >> 14) - 4 * dev::kSiluTableBase;
+          const float t = entry(min(offset, kHalf - 4), __float_as_uint(g) >> 31);
+          s[2 * j + h] = offset < kHalf ? t : dev::silu_outside(g);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
-  }
-  if (!looked_up) {
+  } else {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       s[2 * j] = dev::silu_seq(__uint_as_float(gw[j] << 16));

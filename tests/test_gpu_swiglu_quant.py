@@ -10,7 +10,8 @@ torch = pytest.importorskip("torch")
 
 from oracle import prquant as pq                       # noqa: E402
 from paper_2609_22106_amd import inputs                # noqa: E402
-from tests.gpu_util import assert_gemm_close, dev, host, rows_per_block, say   # noqa: E402
+from tests.gpu_util import (assert_gemm_close, dev, host, replay_us, rows_per_block,  # noqa: E402
+                            say)
 from tests.packing import pack_rows                    # noqa: E402
 
 pytestmark = pytest.mark.gpu
@@ -167,3 +168,53 @@ def test_silu_lookup_equals_sequence_for_every_gate():
             rq, rs = pq.swiglu_quant(g, u)
             np.testing.assert_array_equal(got[1][0].reshape(M, -1), rq)
             np.testing.assert_array_equal(got[1][1].reshape(M, -1), rs)
+
+
+def test_silu_lookup_of_infinities_and_nan():
+    """Gates that are infinite or NaN among finite ones of every size: the looked-up
+    kernel writes what the computed one does."""
+    import ctypes
+    from paper_2609_22106_amd import build
+    prq = _prq()
+    lib = ctypes.CDLL(build.PROBE_LIB)
+    p = ctypes.c_void_p
+    fn = lib.prq_tune_swiglu_quant
+    fn.argtypes = [p, p, ctypes.c_int64, ctypes.c_int, ctypes.c_int, p, p, ctypes.c_int, ctypes.c_int,
+                   ctypes.c_int, p]
+    rng = np.random.default_rng(12)
+    M, K = 96, 4096
+    g = np.concatenate([np.arange(65536), rng.permutation(65536), rng.integers(0, 65536, M * K - 131072)])
+    g = g.astype(np.uint16).reshape(M, K)
+    u = rng.choice(np.array([0x3F80, 0xBF80, 0x4049, 0x0000], np.uint16), (M, K))
+    dg, du = dev(g), dev(u)
+    cb, sb = prq.prq_packed_act_bytes(M, K)
+    say("silu infinities case:", M, K)
+    for packed, nq, ns in ((0, M * K // 2, M * K // 32), (1, cb, sb)):
+        got = []
+        for mode in (1, 2):
+            A = torch.full((nq,), 0x5A, dtype=torch.uint8, device="cuda")
+            As = torch.full((ns,), 0xA5, dtype=torch.uint8, device="cuda")
+            assert fn(dg.data_ptr(), du.data_ptr(), K, M, K, A.data_ptr(), As.data_ptr(), packed, mode, 256,
+                      torch.cuda.current_stream().cuda_stream) == 0
+            torch.cuda.synchronize()
+            got.append((host(A), host(As)))
+        np.testing.assert_array_equal(got[0][1], got[1][1])
+        np.testing.assert_array_equal(got[0][0], got[1][0])
+
+
+@pytest.mark.parametrize("packed", [False, True])
+def test_gates_outside_the_table_take_about_as_long(packed):
+    """One gate of twenty zero (half of all waves' units hold one): measured 1.0-1.2
+    times the time of gates that all lie inside; the SiLU sequence in their place
+    takes 1.7 to 1.9 times."""
+    prq = _prq()
+    M, K = 4096, 4192
+    g = torch.randn(M, K, device="cuda").bfloat16()
+    sparse = torch.where(torch.rand(M, K, device="cuda") < 0.05, torch.zeros_like(g), g)
+    up = torch.randn(M, K, device="cuda").bfloat16()
+    out = prq.prq_swiglu_quant(g, up, K, packed=packed)
+    torch.cuda.synchronize()
+    inside = replay_us(lambda: prq.prq_swiglu_quant(g, up, K, packed=packed, out=out))
+    outside = replay_us(lambda: prq.prq_swiglu_quant(sparse, up, K, packed=packed, out=out))
+    say("gates outside the table:", packed, round(inside, 2), round(outside, 2))
+    assert outside < 1.45 * inside

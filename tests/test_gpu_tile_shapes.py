@@ -66,6 +66,29 @@ def test_tile_shape_dense(shape, M, N, K_aug):
                       f"shape {shape} {M}x{N}x{K_aug}")
 
 
+@pytest.mark.parametrize("packed", [True, False])
+@pytest.mark.parametrize("shape", SHAPE_IDS)
+def test_tile_shape_step_remainders(shape, packed):
+    """One to nine K steps: fewer than the stages, whole groups of them, and every
+    remainder after one and two groups; the last step whole and partial."""
+    from paper_2609_22106_amd import prq
+    from tests.packing import pack_rows
+    M, N = 130, 144
+    for K_aug in (96, 128, 224, 256, 384, 480, 512, 608, 640, 768, 896, 1024, 1056, 1152):
+        rng = np.random.default_rng(K_aug + shape)
+        Aq, Asc = inputs.random_mxfp4(rng, M, K_aug)
+        Wq, Wsc = inputs.random_mxfp4(rng, N, K_aug)
+        W = prq.prq_pack_weight(dev(Wq), dev(Wsc))
+        A, As = (map(dev, pack_rows(Aq, Asc)) if packed else (dev(Aq), dev(Asc)))
+        Y = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+        say("tile step remainder case:", shape, packed, K_aug)
+        assert _split_lib().prq_tune_gemm_tile_split(
+            A.data_ptr(), As.data_ptr(), M, W.Wp.data_ptr(), W.Wps.data_ptr(), N, K_aug, Y.data_ptr(),
+            shape, 1, int(packed), None, 0, torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        assert_gemm_close(host(Y), pq.gemm(Aq, Asc, Wq, Wsc), f"shape {shape} packed {packed} K_aug {K_aug}")
+
+
 GROUPED = [([0, 300, 0, 5, 260], 272, 1024),   # dword
            ([3, 0, 17, 1, 0], 48, 1088),       # byte
            ([0, 0, 200], 128, 832)]            # byte, the expert reduction length

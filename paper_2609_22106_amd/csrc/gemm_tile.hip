@@ -991,17 +991,25 @@ hipError_t launch_region(const uint8_t* Aq, const uint8_t* Asc, int M, const int
 }
 
 // Time of one tile shape over a call, in us:
-//   launch + (K steps + fill) * rate(u) + store * M * N / 10^6,
+//   launch + (K steps + fill) * (rate(u) + ranges * (cols * N + rows * M) / 10^4)
+//     + store * M * N / 10^6,
 //   rate(u) = whole * ceil(u) + spread * u + (128 x 128: pair * ceil(u / 2),
 //                                             else: pair * min(u, 1)),
-// u = workgroups / CUs.  A 128 x 128 workgroup leaves room for a second one on its
-// CU.  Fitted to the forced shapes over 17 row counts (66 .. 8192) of 9 (N, K + k)
-// from 2048 x 832 to 2560 x 9984, each layout (weights rotated; mean error 3 %; the
-// shape it picks is 0.2 % slower than the best one on average and 7 % at most,
-// where busiest-CU efficiencies by load class were 2 % and 34 %: 1537 x 9728 x 2624
-// 43.1 -> 35.2 us, 768 x 1936 x 5344 19.4 -> 14.5, 2500 x 2560 x 9984 47.7 -> 41.7).
+// u = workgroups / CUs (a 128 x 128 workgroup leaves room for a second one on its
+// CU), ranges = K ranges.  Measured: every shape and K range count that the workspace
+// rule allows, over up to 19 row counts (66 .. 8192) of 13 (N, K + k) from 512 x 7168 to
+// 13824 x 5248, with the weight from HBM, as between a model's layers (0.65 of the
+// weight), and in the caches (0.35); the shapes' order differs between the two: packed
+// 2048 x 2560 x 9984 40.9 us from HBM and 42.4 cached in 128 x 128, 43.9 and 38.8 in 256 x
+// 128.  Fitted to the time of the choice it leads to, and a little to the times
+// themselves: the choice is 0.3 % slower than the best on average, packed, and 0.5 %
+// row-major, 11 and 8 % at most (fitted to each half of the (N, K + k) and tried on the
+// other: 1 %).  A fit to the times alone (least squares, weights of few sizes partly
+// cached) chose 1.5 and 2.3 % slower, 24 and 35 % at most: 768 x 2560 x 9984 packed 27.2
+// for 23.5 in two K ranges.  Planned calls against that fit's, over 316 sizes of 17 (N, K +
+// k), each from HBM and cached: packed 1.03x, row-major 1.03x (0.89 and 0.92 the slowest).
 struct ShapeTime {
-  double launch, fill, whole, spread, pair, store;
+  double launch, fill, whole, spread, pair, store, cols, rows;
 };
 // 256 x 320 (8 waves, 64 x 160 each, 3 stages) beats every other plan where it
 // fills the CUs evenly -- 8192 x 2560 x 9984 in one round of 256 tiles, 106 against
@@ -1014,14 +1022,14 @@ struct Shape {
   double eff_packed[3], eff_rows;
 };
 constexpr Shape kShapes[] = {
-    {0, 256, 256, {2.36, 12.653, 0.462, 0.395, -0.113, 0.182}, {1.326, 12.859, 0.584, 0.402, -0.043, 0.156},
-     {1, 0.92, 0.92}, 1},
-    {1, 256, 128, {3.876, 12.767, 0.284, 0.252, -0.13, 0.241}, {2.57, 13.095, 0.391, 0.267, -0.035, 0.101},
-     {0.73, 0.87, 0.8}, 0.63},
-    {2, 128, 128, {1.887, 14.704, 0.167, 0.072, 0.037, 0}, {2.247, 10.736, 0.229, 0.089, 0.063, 0},
-     {0.58, 0.81, 0.68}, 0.5},
-    {3, 256, 320, {1.434, 13.064, 0.561, 0.449, -0.086, 0.156}, {1.315, 9.242, 0.856, 0.369, -0.112, 0.288},
-     {0.9, 0.9, 0.85}, 0.5}};
+    {0, 256, 256, {4.198, 7.362, 0.538, 0.315, -0.282, 0.282, 0.003, 0.151},
+     {4.413, 6.117, 0.81, 0.002, -0.337, 0.763, 0.007, 0.022}, {1, 0.92, 0.92}, 1},
+    {1, 256, 128, {6.2, 12.834, 0.271, 0.24, -0.265, 0, 0.044, 0.414},
+     {5.306, 11.529, 0.426, 0.093, -0.149, 0.453, 0.029, 0.327}, {0.73, 0.87, 0.8}, 0.63},
+    {2, 128, 128, {0, 17.436, 0.154, 0.031, 0.073, 0, 0.05, 0.205},
+     {0, 17.509, 0.16, 0.092, 0.147, 0, 0.029, 0.038}, {0.58, 0.81, 0.68}, 0.5},
+    {3, 256, 320, {5.187, 4.698, 0.686, 0.341, -0.134, 0.368, 0, 0.008},
+     {5.518, 5.753, 0.774, 0.153, -0.057, 0.644, 0, 0.001}, {0.9, 0.9, 0.85}, 0.5}};
 constexpr int kShapeCount = sizeof(kShapes) / sizeof(kShapes[0]);
 
 // Plan of a dense tile GEMM: one shape over all N columns (optionally split
@@ -1038,8 +1046,9 @@ struct TilePlan {
 
 constexpr int kSplits[] = {1, 2, 3, 4, 6, 8};
 constexpr double kSecondLaunchUs = 4.0;   // of a second region beyond the fit's own launch cost
-constexpr double kReduceUs = 4.5;         // the split's reduction: a launch and the first partials
-constexpr double kReduceUsPerMb = 0.13;   // and the partial sums read, Y written (68 measured splits)
+// The split's reduction (row-major, packed A), fitted with the shapes: a launch and the
+// first partials, and a MB of partial sums read and Y written.
+constexpr double kReduceUs[2] = {0.519, 1.661}, kReduceUsPerMb[2] = {0.304, 0.269};
 
 // Split count with every K range non-empty, as the launcher makes it.
 int whole_splits(int steps, int splits) {
@@ -1066,7 +1075,8 @@ TilePlan plan_tile_gemm(int M, int N, int K_aug, int num_cus, bool packed, size_
     const int col16 = s.bn / 16;
     const double u = row_tiles[shape] * ((cols16 + col16 - 1) / col16) * ranges;
     const double rate = t.whole * std::ceil(u - 1e-9) + t.spread * u +
-                        t.pair * (shape == 2 ? std::ceil(0.5 * u - 1e-9) : std::min(u, 1.0));
+                        t.pair * (shape == 2 ? std::ceil(0.5 * u - 1e-9) : std::min(u, 1.0)) +
+                        1e-4 * ranges * (t.cols * 16 * cols16 + t.rows * M);
     return t.launch + (per + t.fill) * rate + t.store * 16e-6 * M * cols16;
   };
   TilePlan best;
@@ -1077,7 +1087,7 @@ TilePlan plan_tile_gemm(int M, int N, int K_aug, int num_cus, bool packed, size_
       const int ranges = whole_splits(steps, sp);
       if (ranges > 1 && split_bytes(ranges, M, N) > room) break;
       double c = cost(i, ntiles, (steps + sp - 1) / sp, ranges);
-      if (ranges > 1) c += kReduceUs + kReduceUsPerMb * 4e-6 * M * N * (ranges + 1);
+      if (ranges > 1) c += kReduceUs[packed] + kReduceUsPerMb[packed] * 4e-6 * M * N * (ranges + 1);
       if (c < best_cost) {
         best_cost = c;
         best = TilePlan{};
@@ -1271,6 +1281,26 @@ size_t tile_workspace_bytes(int M, int N, int K_aug, bool packed, int num_cus) {
   return split_bytes(workspace_splits(M, N, K_aug, num_cus, packed), M, N);
 }
 
+namespace {
+
+// The plan of a call with `room` bytes of workspace: its partial sums take no more
+// than the workspace rule, whatever the call is given.
+TilePlan plan_within_rule(int M, int N, int K_aug, int num_cus, bool packed, size_t room) {
+  const TilePlan plan = plan_tile_gemm(M, N, K_aug, num_cus, packed, room);
+  if (plan.splits == 1) return plan;
+  const size_t rule = tile_workspace_bytes(M, N, K_aug, packed, num_cus);
+  return split_bytes(plan.splits, M, N) <= rule
+             ? plan : plan_tile_gemm(M, N, K_aug, num_cus, packed, std::min(room, rule));
+}
+
+}  // namespace
+
+void tile_plan(int M, int N, int K_aug, bool packed, int num_cus, size_t room, int* out) {
+  const TilePlan p = plan_within_rule(M, N, K_aug, num_cus, packed, room);
+  const int v[6] = {p.parts, p.splits, p.shape[0], p.tiles[0], p.shape[1], p.tiles[1]};
+  std::copy(v, v + 6, out);
+}
+
 hipError_t launch_gemm_tile_planned(const uint8_t* Aq, const uint8_t* Asc, int M,
                                     const uint8_t* Wp, const uint8_t* Wps, int N, int K_aug,
                                     float* Y, bool packed, int num_cus, void* workspace,
@@ -1279,13 +1309,8 @@ hipError_t launch_gemm_tile_planned(const uint8_t* Aq, const uint8_t* Asc, int M
   // workspace (the reduction moves float4s); otherwise the best plan without.
   const bool aligned = (reinterpret_cast<uintptr_t>(Y) & 15u) == 0 &&
                        (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
-  size_t room = workspace && aligned ? workspace_bytes : 0;
-  TilePlan plan = plan_tile_gemm(M, N, K_aug, num_cus, packed, room);
-  if (plan.splits > 1) {   // no more than the call's workspace rule, whatever it is given
-    const size_t rule = tile_workspace_bytes(M, N, K_aug, packed, num_cus);
-    if (split_bytes(plan.splits, M, N) > rule)
-      plan = plan_tile_gemm(M, N, K_aug, num_cus, packed, std::min(room, rule));
-  }
+  const size_t room = workspace && aligned ? workspace_bytes : 0;
+  const TilePlan plan = plan_within_rule(M, N, K_aug, num_cus, packed, room);
   return launch_plan(Aq, Asc, M, Wp, Wps, N, K_aug, Y, packed, plan, static_cast<float*>(workspace), stream);
 }
 

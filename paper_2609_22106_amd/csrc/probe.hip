@@ -393,6 +393,14 @@ int prq_tune_gemm_tile_packed(const uint8_t* Ap, const uint8_t* Aps, int M, cons
              : -3;
 }
 
+// The plan of a dense tile GEMM (host only): out[6] = column regions, K ranges, shape and
+// 16-column tiles of each region.
+int prq_tune_tile_plan(int M, int N, int K_aug, int packed, int num_cus, size_t room, int* out) {
+  if (M <= 0 || N <= 0 || N % 16 || K_aug <= 0 || K_aug % 32 || num_cus <= 0 || !out) return -1;
+  prq::tile_plan(M, N, K_aug, packed != 0, num_cus, room, out);
+  return 0;
+}
+
 // The dense tile GEMM with a forced shape and split count along K (packed or
 // row-major activation); ws: (splits - 1) * M * N floats (ws_bytes checked),
 // 16-byte aligned.

@@ -127,6 +127,9 @@ hipError_t launch_gemm_tile_planned(const uint8_t* Aq, const uint8_t* Asc, int M
                                     const uint8_t* Wp, const uint8_t* Wps, int N, int K_aug,
                                     float* Y, bool packed, int num_cus, void* workspace,
                                     size_t workspace_bytes, hipStream_t stream);
+// Its plan with `room` bytes for partial sums, out[6]: column regions, K ranges, then
+// the shape and 16-column tiles of each region.
+void tile_plan(int M, int N, int K_aug, bool packed, int num_cus, size_t room, int* out);
 // One shape, `splits` K ranges (ws: (splits - 1) * M * N floats, 16-byte
 // aligned like Y); the tuning entry.
 hipError_t launch_gemm_tile_split(const uint8_t* Aq, const uint8_t* Asc, int M, const uint8_t* Wp,

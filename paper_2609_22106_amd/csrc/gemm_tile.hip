@@ -1248,6 +1248,20 @@ hipError_t launch_grouped_persist(const uint8_t* Ap, const uint8_t* Aps, int M,
   return launch_persist_shape<128, 128, 2, 2>(Ap, Aps, M, off, E, Wp, Wps, N, K_aug, Y, num_cus, stream);
 }
 
+// Time of the persistent grouped kernel, in us, for rows routed evenly:
+//   launch + (slot + step * K steps) * (whole * ceil(u) + (1 - whole) * u) + mb * MB moved,
+// u = an XCD's tiles over its workgroups (two of four waves or one of eight a CU).
+// Fitted to 825 calls: 8, 32, 64 and 128 experts, 32 to 1024 rows each, routed evenly
+// and unevenly, of 2048 x 832 to 4096 x 2624 (8 and 6 % off, root mean square).
+double grouped_time(int bm, int bn, int slots, double launch, double slot, double step, double whole, double mb,
+                    int M_total, int N, int K_aug, int E) {
+  const int xcd_experts = (E + kXcds - 1) / kXcds;
+  const double u = mean_row_tiles(static_cast<double>(M_total) / E, bm) * ((N + bn - 1) / bn) * xcd_experts / slots;
+  const double moved = 1e-6 * ((static_cast<double>(E) * N + M_total) * K_aug * 0.531 + 4.0 * M_total * N);
+  return launch + (slot + step * ((K_aug + kStepK - 1) / kStepK)) * (whole * std::ceil(u - 1e-9) + (1 - whole) * u) +
+         mb * moved;
+}
+
 // Shape of the grouped packed GEMM: the persistent kernel where a wave's lanes hold
 // an XCD's experts, with the tile that computes fewer rows for nothing.  256 routed
 // rows and a lead of up to 15 make three 128-row tiles of most experts but two of
@@ -1255,15 +1269,25 @@ hipError_t launch_grouped_persist(const uint8_t* Ap, const uint8_t* Aps, int M,
 // four waves), us, E = 128: rows per expert 256, N = 2048, K + k = 832 104.3 / 120.7;
 // 128 rows 59.8 / 71.1; 256 rows of 1040 x 1536 71.2 / 80.5; 187 rows of 1536 x
 // 1056 81.1 / 76.3; 64 rows 48.4 / 43.1; 37 rows 46.0 / 39.3: wide where its rows at
-// 0.93 of the time each are fewer.  (160 x 128 with three stages 123.6, 192 x 128
-// 151.8; 96 x 128 118.3, and 40.4 at 64 rows.  One workgroup per tile: 158 with 128 x
-// 128, 167 with 256 x 256, 220 with 256 x 128 before the persistent kernel's 119.)
-int choose_grouped_packed_shape(int M_total, int N, int E) {
+// 0.93 of the time each are fewer -- and where its larger tiles, half as many to an
+// XCD's workgroups, don't take a round more: 8 experts of 256 rows, 2048 x 832,
+// 14.8 / 12.3, of 1040 x 1536 18.6 / 13.6; 32 of 256 rows, 1040 x 1536, 1.21x.  The routing
+// is not known here, even routing is taken: with uneven routing wide loses up to 17 %
+// where it gains up to 21 % evenly (128 rows: half of the experts with 0.3 of the
+// rows, 1.10-1.17x the time; 256 rows 0.99-1.07x, 384 on 0.93-0.97x).  (160 x 128 with
+// three stages 123.6, 192 x 128 151.8; 96 x 128 118.3, and 40.4 at 64 rows.  One
+// workgroup per tile: 158 with 128 x 128, 167 with 256 x 256, 220 with 256 x 128 before
+// the persistent kernel's 119.)
+int choose_grouped_packed_shape(int M_total, int N, int K_aug, int E, int num_cus) {
   if (E > 64 * kXcds) return 2;
   const double rows = static_cast<double>(M_total) / E;
   const double wide = 0.93 * 160 * mean_row_tiles(rows, 160) * ((N + 255) / 256 * 256);
   const double narrow = 128 * mean_row_tiles(rows, 128) * ((N + 127) / 128 * 128);
-  return wide < narrow ? kShapePersistWide : kShapePersist;
+  if (wide >= narrow) return kShapePersist;
+  const int xcd_cus = std::max(1, num_cus / kXcds);
+  return grouped_time(160, 256, xcd_cus, 5.025, 3.277, 0.475, 0.817, 0.116, M_total, N, K_aug, E) <
+                 0.985 * grouped_time(128, 128, 2 * xcd_cus, 4.668, 2.111, 0.466, 0.269, 0.125, M_total, N, K_aug, E)
+             ? kShapePersistWide : kShapePersist;
 }
 
 hipError_t launch_grouped_gemm_tile_packed(const uint8_t* Ap, const uint8_t* Aps, int M_total,

@@ -401,6 +401,11 @@ int prq_tune_tile_plan(int M, int N, int K_aug, int packed, int num_cus, size_t 
   return 0;
 }
 
+// The shape of a grouped packed call (host only).
+int prq_tune_grouped_shape(int M_total, int N, int K_aug, int E, int num_cus) {
+  return prq::choose_grouped_packed_shape(M_total, N, K_aug, E, num_cus);
+}
+
 // The dense tile GEMM with a forced shape and split count along K (packed or
 // row-major activation); ws: (splits - 1) * M * N floats (ws_bytes checked),
 // 16-byte aligned.

@@ -145,7 +145,7 @@ hipError_t launch_grouped_gemm_tile_packed(const uint8_t* Ap, const uint8_t* Aps
                                            const int32_t* group_offsets, int E, const uint8_t* Wp,
                                            const uint8_t* Wps, int N, int K_aug, float* Y,
                                            int shape, int num_cus, hipStream_t stream);
-int choose_grouped_packed_shape(int M_total, int N, int E);
+int choose_grouped_packed_shape(int M_total, int N, int K_aug, int E, int num_cus);
 // The tile GEMM with the activation in the packed layout (dense).
 hipError_t launch_gemm_tile_packed(const uint8_t* Ap, const uint8_t* Aps, int M,
                                    const uint8_t* Wp, const uint8_t* Wps, int N, int K_aug,

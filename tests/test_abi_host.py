@@ -482,3 +482,17 @@ def test_planned_tiles_are_the_measured_ones(M, N, K_aug, packed, good):
     assert lib.prq_tune_tile_plan(M, N, K_aug, int(packed), 256, max(ws - HEAD, 0), out) == 0
     assert out[0] == 1 and out[3] == N // 16
     assert (out[1], out[2]) in good
+
+
+# (experts, rows each, N, K_aug, tile): 5 = 160 x 256, 4 = 128 x 128, measured.
+GROUPED_SHAPES = [(128, 256, 2048, 832, 5), (128, 128, 1536, 1056, 5), (128, 64, 2048, 832, 4),
+                  (128, 187, 1536, 1056, 4), (64, 256, 2048, 832, 5), (32, 256, 4096, 2624, 5),
+                  (32, 256, 1040, 1536, 4), (8, 256, 2048, 832, 4), (8, 128, 1536, 1056, 4),
+                  (8, 256, 1040, 1536, 4), (8, 384, 2048, 832, 4), (600, 256, 2048, 832, 2)]
+
+
+@pytest.mark.parametrize("E,rows,N,K_aug,shape", GROUPED_SHAPES)
+def test_grouped_tiles_are_the_measured_ones(E, rows, N, K_aug, shape):
+    import ctypes
+    from paper_2609_22106_amd import build
+    assert ctypes.CDLL(build.PROBE_LIB).prq_tune_grouped_shape(E * rows, N, K_aug, E, 256) == shape

@@ -939,15 +939,15 @@ hipError_t launch_shape_scales(const uint8_t* Aq, const uint8_t* Asc, int M, con
     // 9984: 31.6 -> 28.8 us; 2048 x 2560 went 44.4 -> 51.5, 512 and 4096 x 1024
     // unchanged).
     const int group_rows = kBM == 256 || n_mtiles <= 8 ? 4 : 0;
-    // Non-temporal Y stores where all of Y stays below the L2s' 32 MB: ordinary
+    // Non-temporal Y stores where all of Y would stay in the L2s' 32 MB: ordinary
     // ones leave it dirty there, and the kernel ends only when it has been written
-    // back (us, non-temporal / ordinary, and with an elementwise pass over Y after:
-    // 4096 x 1024 x 2624 11.5 / 13.4, 22.0 / 23.4; 1537 x 2560 x 4192 20.0 / 22.0,
-    // 26.6 / 28.2; 100 x 9728 x 2624 12.3 / 12.5, 15.4 / 15.9).  A larger Y is evicted
-    // as it is written either way, and its reader finds less of it in the caches
-    // (2048 x 2560 x 9984 42.6 / 43.0, 50.8 / 50.1; 4096 x 9728 x 2624 77.5 / 74.0,
-    // 125 / 118).  Partial sums are read back at once: ordinary.
-    const int stream_y = splits == 1 && static_cast<int64_t>(M) * N <= 5000000;
+    // back.  A larger Y is evicted as it is written either way, and its reader finds
+    // less of it in the caches.  The line, 28 MB, is where the gain with an elementwise
+    // pass over Y after the call ends (ordinary / non-temporal time, median of 7 (N, K + k)
+    // packed and 7 row-major, alone and with that pass: 4.4 million values 1.09 and 1.02,
+    // 5.3 million 1.11 and 1.03, 7 million 1.09 and 1.02, 8 million 1.08 and 0.99, 10
+    // million 1.03 and 0.96).  Partial sums are read back at once: ordinary.
+    const int stream_y = splits == 1 && static_cast<int64_t>(M) * N <= 7000000;
     gemm_tile_kernel<kBM, kBN, kWM, kWN, kNS, false, kAMode><<<grid, kWM * kWN * 64, 0, stream>>>(
         Aq, Asc, M, nullptr, 1, n_mtiles, tile_base, region_tiles, Wp, Wps, N, K_aug, Y, splits,
         split_steps, ws, group_rows, stream_y);

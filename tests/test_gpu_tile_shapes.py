@@ -159,10 +159,10 @@ def test_tile_split_k(shape, packed, M, N, K_aug, splits):
 
 
 # Planned calls (row-major, packed) without room for a split: one region and two;
-# Y just below and above the size that is stored non-temporally; the narrowest N,
+# Y on both sides of the size up to which it is stored non-temporally (7 million values); the narrowest N,
 # fewer rows than a tile, more tiles than several rounds; N no multiple of a tile.
 PLANNED = [(66, 16, 1056), (70, 13824, 640), (300, 1936, 1312), (1220, 4096, 288), (1222, 4096, 288),
-           (1537, 9728, 416), (2500, 9728, 288), (4096, 6144, 160), (6000, 4112, 160), (8200, 272, 544)]
+           (1708, 4096, 288), (1710, 4096, 288), (1537, 9728, 416), (2500, 9728, 288), (4096, 6144, 160), (6000, 4112, 160), (8200, 272, 544)]
 
 
 @pytest.mark.parametrize("M,N,K_aug", PLANNED)

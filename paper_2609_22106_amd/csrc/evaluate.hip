@@ -38,6 +38,9 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // chunk loads into registers while the staged one is multiplied, one barrier a
 // chunk (two LDS buffers).  256 x 2560 x 9728: a scalar fma version took 1.79 ms,
 // this one 0.10 (128 TFLOP/s; 160 workgroups, bound by the chunks' load latency).
+// The search's NRMSE over 21 layers (16 to 256 rows, 1024 x 2560 to 2560 x 9728) is off
+// from 64 bits by 1.8e-8 (root mean square; 5.1e-8 at most), by 3.3e-8 (1.2e-7) with
+// the scalar sum in k order.
 __global__ __launch_bounds__(256) void reference_product_kernel(const uint16_t* __restrict__ X,
                                                                 const uint16_t* __restrict__ W,
                                                                 int M, int N, int K,

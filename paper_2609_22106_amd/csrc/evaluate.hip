@@ -154,6 +154,10 @@ struct DeviceArena {
     if (st_ != PRQ_OK) return st_; \
   } while (0)
 
+// Alphas whose exports are chosen together (one read of W for their column errors):
+// the scratch of a call and its launches don't grow with the number of candidates.
+constexpr int32_t kAlphaBatch = 64;
+
 int hip_status(hipError_t e) { return e == hipSuccess ? PRQ_OK : PRQ_EDEVICE; }
 
 // Evaluation of one or more alphas on M rows X (host bf16), against the
@@ -179,7 +183,9 @@ int evaluate_alphas(const uint16_t* W_bf16, int32_t N, int32_t K, const uint16_t
   const int64_t per_block = (outs + err_blocks - 1) / err_blocks;
   const bool own_rows = X_bf16 == Xcal_bf16 && M == T;   // evaluated on the calibration rows
   const size_t nW = static_cast<size_t>(N) * K, nX = static_cast<size_t>(M) * K,
-               nCal = static_cast<size_t>(T) * K, nScale = static_cast<size_t>(n_alpha) * K;
+               nCal = static_cast<size_t>(T) * K;
+  const int32_t batch = std::min(n_alpha, kAlphaBatch);
+  const size_t nScale = static_cast<size_t>(batch) * K;
 
   DeviceArena mem;
   const size_t oW = mem.reserve<uint16_t>(nW), oX = mem.reserve<uint16_t>(nX),
@@ -196,7 +202,7 @@ int evaluate_alphas(const uint16_t* W_bf16, int32_t N, int32_t K, const uint16_t
                oAsc = mem.reserve<uint8_t>(static_cast<size_t>(M) * K_aug / 32);
   const size_t oWp = mem.reserve<uint8_t>(code_bytes), oWps = mem.reserve<uint8_t>(scale_bytes);
   const size_t oWs = mem.reserve<uint8_t>(ws_bytes);
-  const size_t nPartial = static_cast<size_t>(2) * err_blocks * n_alpha;
+  const size_t nPartial = static_cast<size_t>(2) * err_blocks * batch;
   const size_t oPartial = mem.reserve<double>(nPartial);
   PRQ_TRY(mem.allocate());
   uint16_t *const dW = mem.at<uint16_t>(oW), *const dX = mem.at<uint16_t>(oX),
@@ -222,43 +228,49 @@ int evaluate_alphas(const uint16_t* W_bf16, int32_t N, int32_t K, const uint16_t
   reference_product_kernel<<<dim3((N + kRefTile - 1) / kRefTile, (M + kRefTile - 1) / kRefTile), 256, 0,
                              stream>>>(dX, dW, M, N, K, dYref);
   PRQ_TRY(hip_status(hipGetLastError()));
-  std::vector<float> scales(2 * nScale);
-  for (int a = 0; a < n_alpha; ++a)
-    channel_scales(maxima.data(), maxima.data() + K, K, alphas[a], scale_mode,
-                   scales.data() + static_cast<size_t>(a) * K, scales.data() + nScale + static_cast<size_t>(a) * K);
-  PRQ_TRY(hip_status(hipMemcpyAsync(dScale, scales.data(), scales.size() * sizeof(float),
-                                    hipMemcpyHostToDevice, stream)));
-  PRQ_TRY(hip_status(launch_tail_selection(dW, N, K, k_tail, n_alpha, dScale, dScale + nScale,
-                                           mem.at<double>(oErr), mem.at<int32_t>(oRank),
-                                           mem.at<int32_t>(oPerm), mem.at<float>(oScalePos),
-                                           mem.at<float>(oInvPos), stream)));
+  std::vector<float> scales(2 * nScale);   // as dScale: scales, then inverse scales
+  std::vector<double> partial(nPartial);
   uint8_t *const dWq = mem.at<uint8_t>(oWq), *const dWsc = mem.at<uint8_t>(oWsc),
           *const dAq = mem.at<uint8_t>(oAq), *const dAsc = mem.at<uint8_t>(oAsc),
           *const dWp = mem.at<uint8_t>(oWp), *const dWps = mem.at<uint8_t>(oWps);
-  for (int a = 0; a < n_alpha; ++a) {
-    const size_t at = static_cast<size_t>(a) * K;
-    const int32_t* perm = mem.at<int32_t>(oPerm) + at;
-    PRQ_TRY(hip_status(launch_augment_weight(dW, N, K, k_tail, perm, mem.at<float>(oScalePos) + at,
-                                             (flags & PRQ_PREPARE_E8M0_SEARCH) != 0, dWq, dWsc, stream)));
-    PRQ_TRY(prq_pack_weight(dWq, dWsc, 1, N, static_cast<int32_t>(K_aug), dWp, dWps, stream));
-    PRQ_TRY(prq_quant_act(dX, K, M, K, k_tail, mem.at<float>(oInvPos) + at, perm, nullptr, 1, dAq, dAsc, stream));
-    PRQ_TRY(prq_gemm(dAq, dAsc, M, dWp, dWps, N, static_cast<int32_t>(K_aug), dY, mem.at<uint8_t>(oWs),
-                     ws_bytes, stream));
-    squared_error_kernel<<<err_blocks, kErrThreads, 0, stream>>>(
-        dY, dYref, outs, per_block, dPartial + static_cast<size_t>(2) * err_blocks * a);
-    PRQ_TRY(hip_status(hipGetLastError()));
-  }
-  std::vector<double> partial(nPartial);
-  PRQ_TRY(hip_status(hipMemcpyAsync(partial.data(), dPartial, nPartial * sizeof(double),
-                                    hipMemcpyDeviceToHost, stream)));
-  PRQ_TRY(hip_status(hipStreamSynchronize(stream)));
-  for (int a = 0; a < n_alpha; ++a) {
-    double e = 0.0, r = 0.0;
-    for (int b = 0; b < err_blocks; ++b) {   // fixed order
-      e += partial[2 * (static_cast<size_t>(err_blocks) * a + b)];
-      r += partial[2 * (static_cast<size_t>(err_blocks) * a + b) + 1];
+  for (int32_t a0 = 0; a0 < n_alpha; a0 += batch) {
+    const int32_t n = std::min(batch, n_alpha - a0);
+    for (int32_t a = 0; a < n; ++a) {
+      const size_t at = static_cast<size_t>(a) * K;
+      channel_scales(maxima.data(), maxima.data() + K, K, alphas[a0 + a], scale_mode, scales.data() + at,
+                     scales.data() + nScale + at);
     }
-    nrmse[a] = r > 0.0 ? std::sqrt(e / r) : (e > 0.0 ? INFINITY : 0.0);
+    PRQ_TRY(hip_status(hipMemcpyAsync(dScale, scales.data(), scales.size() * sizeof(float),
+                                      hipMemcpyHostToDevice, stream)));
+    PRQ_TRY(hip_status(launch_tail_selection(dW, N, K, k_tail, n, dScale, dScale + nScale,
+                                             mem.at<double>(oErr), mem.at<int32_t>(oRank),
+                                             mem.at<int32_t>(oPerm), mem.at<float>(oScalePos),
+                                             mem.at<float>(oInvPos), stream)));
+    for (int32_t a = 0; a < n; ++a) {
+      const size_t at = static_cast<size_t>(a) * K;
+      const int32_t* perm = mem.at<int32_t>(oPerm) + at;
+      PRQ_TRY(hip_status(launch_augment_weight(dW, N, K, k_tail, perm, mem.at<float>(oScalePos) + at,
+                                               (flags & PRQ_PREPARE_E8M0_SEARCH) != 0, dWq, dWsc, stream)));
+      PRQ_TRY(prq_pack_weight(dWq, dWsc, 1, N, static_cast<int32_t>(K_aug), dWp, dWps, stream));
+      PRQ_TRY(prq_quant_act(dX, K, M, K, k_tail, mem.at<float>(oInvPos) + at, perm, nullptr, 1, dAq, dAsc, stream));
+      PRQ_TRY(prq_gemm(dAq, dAsc, M, dWp, dWps, N, static_cast<int32_t>(K_aug), dY, mem.at<uint8_t>(oWs),
+                       ws_bytes, stream));
+      squared_error_kernel<<<err_blocks, kErrThreads, 0, stream>>>(
+          dY, dYref, outs, per_block, dPartial + static_cast<size_t>(2) * err_blocks * a);
+      PRQ_TRY(hip_status(hipGetLastError()));
+    }
+    PRQ_TRY(hip_status(hipMemcpyAsync(partial.data(), dPartial,
+                                      static_cast<size_t>(2) * err_blocks * n * sizeof(double),
+                                      hipMemcpyDeviceToHost, stream)));
+    PRQ_TRY(hip_status(hipStreamSynchronize(stream)));   // also: the host's scales are free again
+    for (int32_t a = 0; a < n; ++a) {
+      double e = 0.0, r = 0.0;
+      for (int b = 0; b < err_blocks; ++b) {   // fixed order
+        e += partial[2 * (static_cast<size_t>(err_blocks) * a + b)];
+        r += partial[2 * (static_cast<size_t>(err_blocks) * a + b) + 1];
+      }
+      nrmse[a0 + a] = r > 0.0 ? std::sqrt(e / r) : (e > 0.0 ? INFINITY : 0.0);
+    }
   }
   return PRQ_OK;
 }

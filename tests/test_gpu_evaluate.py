@@ -141,3 +141,17 @@ def test_alpha_search_scales_and_errors_follow_prepare():
             want = pq.nrmse(host(y).astype(np.float64), ref)
             say("search error", mode, a, got, want)
             assert abs(got - want) <= 2e-6 * want
+
+
+def test_search_over_many_alphas():
+    """More candidates than are taken together, and more than a launch dimension
+    holds (65535): each one's error is the one it has in a search of its own."""
+    from paper_2609_22106_amd import prq
+    c = inputs.make_dense("many", N=16, K=64, M=8, T=5, k_tail=32, n_out=2, seed=9)
+    for n in (65, 70000):
+        alphas = np.linspace(0.0, 1.0, n)
+        say("many alphas case:", n)
+        best, errs = prq.prq_search_alpha(c.W, c.Xcal, alphas, 32)
+        assert best == alphas[int(np.argmin(errs))]
+        for i in np.unique(np.concatenate([[0, 63, 64, n - 1], np.arange(0, n, max(1, n // 7))])):
+            assert prq.prq_search_alpha(c.W, c.Xcal, alphas[i:i + 1], 32)[1][0] == errs[i], i

@@ -393,6 +393,19 @@ int prq_tune_gemm_tile_packed(const uint8_t* Ap, const uint8_t* Aps, int M, cons
              : -3;
 }
 
+// Launches of prq_pack_weight (host only; 0: refused), and packing with at most
+// max_blocks workgroups a launch.
+int prq_tune_pack_launches(int E, int N, int K_aug) {
+  int64_t codes, scales;
+  return prq::pack_launches(N, K_aug, E, prq::kPackMaxBlocks, &codes, &scales);
+}
+
+int prq_tune_pack_weight(const uint8_t* Wq, const uint8_t* Wsc, int E, int N, int K_aug, uint8_t* Wp,
+                         uint8_t* Wps, int64_t max_blocks, hipStream_t stream) {
+  if (E < 1 || N <= 0 || N % 16 || K_aug <= 0 || K_aug % 32 || max_blocks < 1) return -1;
+  return prq::launch_pack_weight(Wq, Wsc, N, K_aug, E, Wp, Wps, stream, max_blocks) == hipSuccess ? 0 : -3;
+}
+
 // The plan of a dense tile GEMM (host only): out[6] = column regions, K ranges, shape and
 // 16-column tiles of each region.
 int prq_tune_tile_plan(int M, int N, int K_aug, int packed, int num_cus, size_t room, int* out) {

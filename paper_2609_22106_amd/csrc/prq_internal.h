@@ -107,8 +107,13 @@ hipError_t launch_augment_weight(const uint16_t* W, int N, int K, int k_tail, co
 // pack.hip: the packed weight layout the GEMM kernels read.
 size_t packed_code_bytes(int N, int K_aug, int E);
 size_t packed_scale_bytes(int N, int K_aug, int E);
+// 1, or 2 where the codes' and the scales' workgroups together pass max_blocks, or 0
+// where one of them does (refused); the default is what a launch of 256 threads each holds.
+constexpr int64_t kPackMaxBlocks = ((int64_t{1} << 32) - 1) / 256;
+int pack_launches(int N, int K_aug, int E, int64_t max_blocks, int64_t* code_blocks, int64_t* scale_blocks);
 hipError_t launch_pack_weight(const uint8_t* Wq, const uint8_t* Wsc, int N, int K_aug, int E,
-                              uint8_t* Wp, uint8_t* Wps, hipStream_t stream);
+                              uint8_t* Wp, uint8_t* Wps, hipStream_t stream,
+                              int64_t max_blocks = kPackMaxBlocks);
 
 // gemm_tile.hip / gemm_stream.hip (packed weights Wp/Wps).  group_offsets ==
 // nullptr means one group of M rows.

@@ -496,3 +496,15 @@ def test_grouped_tiles_are_the_measured_ones(E, rows, N, K_aug, shape):
     import ctypes
     from paper_2609_22106_amd import build
     assert ctypes.CDLL(build.PROBE_LIB).prq_tune_grouped_shape(E * rows, N, K_aug, E, 256) == shape
+
+
+def test_pack_launches_at_the_launch_limit():
+    """A launch holds 2^32 - 1 threads, a thread packs 16 bytes of codes or 4 scales: up
+    to 64 GiB of codes are packed, in two launches where the scales' threads do not fit
+    beside them; more is refused."""
+    import ctypes
+    from paper_2609_22106_amd import build
+    f = ctypes.CDLL(build.PROBE_LIB).prq_tune_pack_launches
+    # E = 512, K_aug = 4096: 1 GiB of codes for every 1024 rows
+    assert [f(512, 1024 * gib, 4096) for gib in (1, 51, 52, 63, 64, 100)] == [1, 1, 2, 2, 0, 0]
+    assert f(512, 1024 * 64 - 16, 4096) == 2

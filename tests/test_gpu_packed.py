@@ -681,3 +681,29 @@ def test_packed_pair_layer_shapes(name, N, K):
     rows = rows_per_block(M, rng)
     rq, rs = pq.quant_act(X[rows], inv, perm, k)
     assert_gemm_close(Y[rows], pq.gemm(rq, rs, Wq, Wsc), f"{name} {M}x{N}x{K}+{k}")
+
+
+@pytest.mark.parametrize("E,N,K_aug", [(3, 272, 1056), (1, 16, 32), (2, 48, 640)])
+def test_pack_in_two_launches(E, N, K_aug):
+    """Codes and scales packed by a launch each (where both together pass the launch
+    limit, forced here): the bytes of the one launch."""
+    from paper_2609_22106_amd import build
+    prq = _prq()
+    rng = np.random.default_rng(E + N)
+    Wq, Wsc = inputs.random_mxfp4(rng, (E, N), K_aug)
+    dq, ds = dev(Wq), dev(Wsc)
+    want = prq.prq_pack_weight(dq, ds)
+    lib = ctypes.CDLL(build.PROBE_LIB)
+    P, I = ctypes.c_void_p, ctypes.c_int
+    lib.prq_tune_pack_weight.argtypes = [P, P, I, I, I, P, P, ctypes.c_int64, P]
+    Wp, Wps = torch.full_like(want.Wp, 0x5A), torch.full_like(want.Wps, 0xA5)
+    stream = torch.cuda.current_stream().cuda_stream
+    blocks = -(-want.Wp.numel() // 16 // 256)       # the codes' alone
+    say("pack in two launches case:", E, N, K_aug)
+    assert lib.prq_tune_pack_weight(dq.data_ptr(), ds.data_ptr(), E, N, K_aug, Wp.data_ptr(),
+                                    Wps.data_ptr(), blocks, stream) == 0
+    torch.cuda.synchronize()
+    assert torch.equal(Wp, want.Wp) and torch.equal(Wps, want.Wps)
+    if blocks > 1:
+        assert lib.prq_tune_pack_weight(dq.data_ptr(), ds.data_ptr(), E, N, K_aug, Wp.data_ptr(),
+                                        Wps.data_ptr(), blocks - 1, stream) != 0

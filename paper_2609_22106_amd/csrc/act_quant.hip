@@ -723,6 +723,9 @@ __global__ __launch_bounds__(kDmaThreads) void act_quant_short_kernel(
   for (int i = 0; i < n; ++i) {
     wait_vmcnt_lgkm0<63>();                        // this wave's LDS reads of pass i-1
     __builtin_amdgcn_s_barrier();
+    // The copies into the stages are another branch's asm: without this nothing here
+    // tells the compiler that a stage changes, and it may read it before the barrier.
+    asm volatile("" ::: "memory");
     const int r = r0 + i * rpp + ro;
     if (ro < rpp && r < r1) {                      // quad-uniform: units is a multiple of 4
       if (kGrouped) {

@@ -144,8 +144,8 @@ def test_alpha_search_scales_and_errors_follow_prepare():
 
 
 def test_search_over_many_alphas():
-    """More candidates than are taken together, and more than a launch dimension
-    holds (65535): each one's error is the one it has in a search of its own."""
+    """More candidates than are taken together, and many: each one's error is the
+    one it has in a search of its own."""
     from paper_2609_22106_amd import prq
     c = inputs.make_dense("many", N=16, K=64, M=8, T=5, k_tail=32, n_out=2, seed=9)
     for n in (65, 70000):

@@ -270,15 +270,18 @@ int prq_probe_mfma32(const void* a, const void* b, const void* sa, const void* s
   return hipGetLastError() == hipSuccess ? 0 : -3;
 }
 
-// Activation quantization with a forced kernel (1 few-rows, 2 many-rows with
-// register-staged rows, 3 many-rows with rows copied into LDS stages).
+// Activation quantization with a forced kernel (0 automatic, 1 few-rows, 2 many-rows with
+// register-staged rows, 3 many-rows with rows copied into LDS stages, 5 short rows copied
+// a pass at a time, K < 2048), its workgroups sized for num_cus CUs.
 int prq_tune_act_quant(const void* X, int64_t ld_x, int M, int K, int k_tail, const float* inv,
-                       const int32_t* perm, uint8_t* Aq, uint8_t* Asc, int kernel,
-                       hipStream_t stream) {
-  if (M <= 0 || K <= 0 || K % 32 || k_tail % 32 || k_tail > K || K > 16384 || ld_x < K || (kernel == 5 && K >= 2048))
+                       const int32_t* perm, const int32_t* off, int G, uint8_t* Aq, uint8_t* Asc,
+                       int kernel, int num_cus, hipStream_t stream) {
+  if (M <= 0 || K <= 0 || K % 32 || k_tail < 0 || k_tail % 32 || k_tail > K || K > 16384 || ld_x < K ||
+      kernel < 0 || kernel > 5 || kernel == 4 || (kernel == 5 && K >= 2048) || G < 1 || (G > 1 && !off) ||
+      num_cus <= 0)
     return -1;
   return prq::launch_act_quant_kernel(static_cast<const uint16_t*>(X), ld_x, M, K, k_tail, inv, perm,
-                                      nullptr, 1, Aq, Asc, 256, kernel, stream) == hipSuccess
+                                      off, G, Aq, Asc, num_cus, kernel, stream) == hipSuccess
              ? 0
              : -3;
 }

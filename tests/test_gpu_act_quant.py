@@ -58,8 +58,9 @@ def test_ragged_rows(M):
     _check(c.X, 1024, 64, art["inv_scale"], art["perm"], f"M={M}")
 
 
-@pytest.mark.parametrize("K,k,M", [(768, 64, 131), (4096, 96, 70), (4160, 160, 97), (9728, 224, 65),
-                                   (12320, 288, 66), (16384, 512, 67)])
+# (at least 1025 rows or more than 1024 x 768 channels: fewer are the few-rows kernel's)
+@pytest.mark.parametrize("K,k,M", [(768, 64, 1131), (2048, 64, 389), (4096, 96, 200), (4160, 160, 197),
+                                   (6144, 64, 131), (9728, 224, 85), (12320, 288, 66), (16384, 512, 67)])
 def test_many_row_kernel_shapes(K, k, M):
     """The many-row kernel at every units-per-thread count (K/8 over 512
     threads: 1 with several rows per pass, 1, 2, 3, 4 and the largest K),
@@ -102,7 +103,7 @@ def test_few_row_kernel_largest_rows(M):
 def test_many_row_kernel_grouped_two_units_per_thread():
     rng = np.random.default_rng(12)
     E, K, k = 4, 4160, 160
-    counts = [40, 0, 90, 7]
+    counts = [60, 0, 130, 9]
     off = inputs.routed_offsets(counts)
     X = inputs.f32_to_bf16_bits((rng.standard_normal((int(off[-1]), K)) * 2).astype(np.float32))
     perm = np.stack([rng.permutation(K) for _ in range(E)]).astype(np.int32)
@@ -280,7 +281,7 @@ SHORT = [(32, 32, 700, 1, 32), (768, 64, 333, 1, 768), (768, 64, 331, 7, 776), (
 @pytest.mark.parametrize("K,k,M,G,ld", SHORT)
 def test_short_row_copy_kernel(K, k, M, G, ld):
     """act_quant_short_kernel forced (the tuning entry; AUTO takes it for larger
-    calls): row-major where ungrouped, and packed."""
+    calls): packed, and row-major in several passes a workgroup and in one."""
     import ctypes
     from paper_2609_22106_amd import build, prq
     from tests.packing import pack_rows
@@ -292,7 +293,6 @@ def test_short_row_copy_kernel(K, k, M, G, ld):
     rq, rs = pq.quant_act_grouped(X[:, :K], inv, perm, off, k)
     lib = ctypes.CDLL(build.PROBE_LIB)
     P, I, L = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64
-    lib.prq_tune_act_quant.argtypes = [P, L, I, I, I, P, P, P, P, I, P]
     lib.prq_tune_act_quant_packed.argtypes = [P, L, I, I, I, P, P, P, I, P, P, I, I, P]
     dX, di, dp, do = dev(X), dev(_pos(inv, perm)), dev(perm), dev(off)
     stream = torch.cuda.current_stream().cuda_stream
@@ -307,11 +307,79 @@ def test_short_row_copy_kernel(K, k, M, G, ld):
     ep, es = pack_rows(rq, rs)
     np.testing.assert_array_equal(host(Aps), es)
     np.testing.assert_array_equal(host(Ap), ep)
-    if G == 1:
-        Aq = torch.empty((M, (K + k) // 2), dtype=torch.uint8, device="cuda")
-        Asc = torch.empty((M, (K + k) // 32), dtype=torch.uint8, device="cuda")
-        assert lib.prq_tune_act_quant(dX.data_ptr(), ld, M, K, k, di.data_ptr(), dp.data_ptr(),
-                                      Aq.data_ptr(), Asc.data_ptr(), 5, stream) == 0
+    for cus in (7, 256):
+        Aq, Asc = _forced_rows(X, K, k, _pos(inv, perm), perm, off if G > 1 else None, G, 5, cus)
+        np.testing.assert_array_equal(Asc, rs)
+        np.testing.assert_array_equal(Aq, rq)
+
+
+def _forced_rows(X, K, k, inv_pos, perm, off, G, kernel, cus):
+    """Row-major codes and scales by a forced kernel with workgroups for `cus` CUs."""
+    import ctypes
+    from paper_2609_22106_amd import build
+    lib = ctypes.CDLL(build.PROBE_LIB)
+    P, I, L = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64
+    lib.prq_tune_act_quant.argtypes = [P, L, I, I, I, P, P, P, I, P, P, I, I, P]
+    M = X.shape[0]
+    Aq = torch.full((M, (K + k) // 2), 0x5A, dtype=torch.uint8, device="cuda")
+    Asc = torch.full((M, (K + k) // 32), 0xA5, dtype=torch.uint8, device="cuda")
+    dX, di, dp = dev(X), dev(inv_pos), dev(perm)
+    do = None if off is None else dev(off)
+    assert lib.prq_tune_act_quant(dX.data_ptr(), X.shape[1], M, K, k, di.data_ptr(), dp.data_ptr(),
+                                  None if do is None else do.data_ptr(), G, Aq.data_ptr(), Asc.data_ptr(),
+                                  kernel, cus, torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    return host(Aq), host(Asc)
+
+
+# (K, k, M, CUs): one to four units a thread and several rows a pass, each in at least
+# five passes or rows a workgroup (stages reused), a ragged last one.
+MANY_ROWS = [(32, 0, 1500, 1), (768, 64, 133, 4), (1440, 96, 91, 3), (2048, 32, 97, 5), (4096, 96, 70, 3),
+             (4160, 160, 97, 4), (7136, 32, 50, 2), (9728, 224, 65, 3), (12320, 288, 33, 2), (16384, 512, 35, 2)]
+
+
+@pytest.mark.parametrize("kernel,K,k,M,cus", [(q, *c) for q in (2, 3, 5) for c in MANY_ROWS
+                                              if q != 5 or c[0] < 2048])
+@pytest.mark.parametrize("G", [1, 6])
+def test_many_row_kernels_row_major(kernel, G, K, k, M, cus):
+    """Row-major output of each many-rows kernel (2: staged through registers, 3: rows
+    copied, 5: short rows copied), forced, with groups changing between passes and
+    inside them, empty ones among them."""
+    rng = np.random.default_rng(K + M + G)
+    X = inputs.f32_to_bf16_bits((rng.standard_normal((M, K + 8)) * 3).astype(np.float32))
+    perm = np.stack([rng.permutation(K) for _ in range(G)]).astype(np.int32)
+    inv = rng.uniform(0.1, 4.0, (G, K)).astype(np.float32)
+    off = inputs.routed_offsets(np.bincount(rng.choice([0, 1, 1, 3, 5, 5, 5], M) if G > 1 else np.zeros(M, int),
+                                            minlength=G))
+    say("many rows case:", kernel, G, K, k, M, cus)
+    Aq, Asc = _forced_rows(X, K, k, _pos(inv, perm), perm, off if G > 1 else None, G, kernel, cus)
+    rq, rs = pq.quant_act_grouped(X[:, :K], inv, perm, off, k)
+    np.testing.assert_array_equal(Asc, rs)
+    np.testing.assert_array_equal(Aq, rq)
+
+
+@pytest.mark.parametrize("M", [7100, 7300])
+@pytest.mark.parametrize("packed", [False, True])
+def test_grouped_short_rows_on_both_sides_of_the_copy_kernels_line(packed, M):
+    """5.5 million channels: below it rows are staged through registers, from it on they
+    are copied (grouped calls as an expert prefill makes them)."""
+    from paper_2609_22106_amd import prq
+    from tests.packing import pack_rows
+    K, k, G = 768, 64, 40
+    rng = np.random.default_rng(M)
+    X = inputs.f32_to_bf16_bits((rng.standard_normal((M, K)) * 3).astype(np.float32))
+    perm = np.stack([rng.permutation(K) for _ in range(G)]).astype(np.int32)
+    inv = rng.uniform(0.1, 4.0, (G, K)).astype(np.float32)
+    off = inputs.routed_offsets(np.bincount(rng.integers(0, G - 1, M), minlength=G))
+    rq, rs = pq.quant_act_grouped(X, inv, perm, off, k)
+    say("short rows line case:", packed, M)
+    if packed:
+        A = prq.prq_quant_act_packed(dev(X), K, k, dev(_pos(inv, perm)), dev(perm), group_offsets=dev(off), G=G)
         torch.cuda.synchronize()
-        np.testing.assert_array_equal(host(Asc), rs)
-        np.testing.assert_array_equal(host(Aq), rq)
+        ep, es = pack_rows(rq, rs)
+        np.testing.assert_array_equal(host(A.Aps), es)
+        np.testing.assert_array_equal(host(A.Ap), ep)
+    else:
+        Aq, Asc = _gpu_quant(X, K, k, inv, perm, offsets=off, G=G)
+        np.testing.assert_array_equal(Asc, rs)
+        np.testing.assert_array_equal(Aq, rq)

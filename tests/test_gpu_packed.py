@@ -441,12 +441,16 @@ def _pos_grouped(inv, perm):
     return np.take_along_axis(np.asarray(inv), np.asarray(perm), axis=1)
 
 
-# Experts sharing 16-row blocks, empty experts (first, middle and last), and
-# K below (register-staged kernel) and above (LDS-staged kernel) 2048.
+# Experts sharing 16-row blocks, empty experts (first, middle and last): few rows, and
+# (past 1024 x 768 channels) K below (register-staged kernel) and above (LDS-staged
+# kernel) 2048.
 GROUPED_QUANT = [([3, 0, 20, 1, 13], 768, 64),
                  ([0, 37, 16, 0, 64, 5, 0], 768, 64),
                  ([40, 0, 90, 7], 4160, 160),
-                 ([17, 1, 0, 33], 2048, 32)]
+                 ([17, 1, 0, 33], 2048, 32),
+                 ([0, 300, 16, 0, 705, 90, 0], 768, 64),
+                 ([70, 0, 120, 17], 4160, 160),
+                 ([170, 1, 0, 230], 2048, 32)]
 
 
 @pytest.mark.parametrize("counts,K,k", GROUPED_QUANT)

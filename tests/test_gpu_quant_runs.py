@@ -41,8 +41,11 @@ KINDS = ["tail", "tail+swaps", "identity"]
 
 
 @pytest.mark.parametrize("kind", KINDS)
-@pytest.mark.parametrize("M,K,k", [(65, 768, 64), (300, 2560, 64), (97, 4096, 96), (70, 9728, 256)])
+@pytest.mark.parametrize("M,K,k", [(65, 768, 64), (300, 2560, 64), (97, 4096, 96), (70, 9728, 256),
+                                   (1100, 768, 64), (310, 2560, 64), (200, 4096, 96), (85, 9728, 256)])
 def test_row_major_quantizer_runs(M, K, k, kind):
+    """Rows the few-rows kernel takes (the first four), and more: staged through
+    registers (K = 768) and copied whole."""
     prq = _prq()
     X, inv, perm = _case(M, K, k, kind, M + K)
     say("runs case: row-major", M, K, k, kind)
@@ -77,10 +80,12 @@ def _tune_packed(X, K, k, inv_pos, perm, off, G, kernel, num_cus):
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("kernel", [0, 2, 3, 4])
 @pytest.mark.parametrize("M,K,k,cus", [(97, 2400, 96, 3), (41, 9728, 256, 2), (300, 768, 64, 7),
-                                       (37, 6144, 128, 2)])
+                                       (37, 6144, 128, 2), (340, 2400, 96, 3), (85, 9728, 256, 2),
+                                       (1100, 768, 64, 7), (130, 6144, 128, 2)])
 def test_packed_quantizer_kernels_runs(M, K, k, cus, kernel, kind):
-    """The automatic choice (0; at K = 6144 with 19 rows per workgroup, LDS
-    row stages with the output window), register-staged rows (2), LDS row
+    """The automatic choice (0; the few-rows kernel in the first four, then LDS
+    row stages, register-staged rows at K = 768, and at K = 6144 with 65 rows
+    per workgroup the output window), register-staged rows (2), LDS row
     stages with the 8-row output window (3) and with direct output (4),
     multi-row workgroup ranges."""
     X, inv, perm = _case(M, K, k, kind, M * 3 + K + kernel)

@@ -1,10 +1,9 @@
 """Every tile shape of the LDS-tiled GEMM (Eq. 3 over K + k), forced one at a
 time through the library's tuning entry point, against the oracle's float64
-GEMM: max |dY| <= 1e-3 max |Y|.  Covers both ways the kernel stages the
-activation scales (one aligned dword per row and step when K + k is a multiple
-of 128, single bytes otherwise), ragged M, N and K + k, row and feature tiles
-cut by the operand edges, steps fewer than the pipeline's stages, and grouped
-calls with empty experts."""
+GEMM: max |dY| <= 1e-3 max |Y|.  Covers row-major activation scales at rows that
+start on dwords (K + k a multiple of 128) and at any byte, ragged M, N and K + k,
+row and feature tiles cut by the operand edges, steps fewer than the pipeline's
+stages and every remainder of them, and grouped calls with empty experts."""
 import ctypes
 
 import numpy as np
@@ -46,13 +45,13 @@ def _run(shape, Aq, Asc, Wq, Wsc, off=None, E=1):
     return host(Y)
 
 
-DENSE = [(300, 384, 1024),    # dword scales, ragged rows
-         (513, 272, 1152),    # dword, ragged rows and features (272 = 17 tiles of 16)
-         (40, 512, 9984),     # dword, the down_proj reduction length, one row tile
-         (257, 272, 1088),    # byte scales (1088 = 8.5 steps of 128)
-         (130, 144, 4192),    # byte, 32.75 steps
-         (17, 48, 96),        # byte, one partial step (fewer steps than stages)
-         (64, 256, 256)]      # dword, two steps
+DENSE = [(300, 384, 1024),    # scale rows on dwords, ragged rows
+         (513, 272, 1152),    # dwords, ragged rows and features (272 = 17 tiles of 16)
+         (40, 512, 9984),     # dwords, the down_proj reduction length, one row tile
+         (257, 272, 1088),    # scale rows at any byte (1088 = 8.5 steps of 128)
+         (130, 144, 4192),    # any byte, 32.75 steps
+         (17, 48, 96),        # any byte, one partial step (fewer steps than stages)
+         (64, 256, 256)]      # dwords, two steps
 
 
 @pytest.mark.parametrize("M,N,K_aug", DENSE)
@@ -89,9 +88,9 @@ def test_tile_shape_step_remainders(shape, packed):
         assert_gemm_close(host(Y), pq.gemm(Aq, Asc, Wq, Wsc), f"shape {shape} packed {packed} K_aug {K_aug}")
 
 
-GROUPED = [([0, 300, 0, 5, 260], 272, 1024),   # dword
-           ([3, 0, 17, 1, 0], 48, 1088),       # byte
-           ([0, 0, 200], 128, 832)]            # byte, the expert reduction length
+GROUPED = [([0, 300, 0, 5, 260], 272, 1024),   # dwords
+           ([3, 0, 17, 1, 0], 48, 1088),       # any byte
+           ([0, 0, 200], 128, 832)]            # any byte, the expert reduction length
 
 
 @pytest.mark.parametrize("counts,N,K_aug", GROUPED)
@@ -122,7 +121,7 @@ def _split_lib():
 # whole 4-step groups, a last range of one step, ragged rows and features.
 SPLIT = [(300, 272, 1024, 3),      # 8 steps -> 3 + 3 + 2
          (513, 144, 9984, 8),      # 78 steps -> 10 x 7 + 8
-         (40, 512, 4192, 4),       # 33 steps -> 9 + 9 + 9 + 6 (byte scales when row-major)
+         (40, 512, 4192, 4),       # 33 steps -> 9 + 9 + 9 + 6 (scale rows at any byte)
          (129, 64, 1152, 9),       # 9 steps -> one step each
          (64, 256, 640, 2)]        # 5 steps -> 3 + 2
 

@@ -391,8 +391,8 @@ int prq_swiglu_quant_packed(const void* gate_bf16, const void* up_bf16, int64_t 
  * configuration, ||Y_hat - X W^T||_F / ||X W^T||_F, where Y_hat is Eq. 3
  * evaluated on the rows X with the device path (prq_prepare_ex's export for the
  * calibration rows Xcal, alpha, k_tail, scale_mode and flags, built on the
- * device with the same bits, then prq_pack_weight, prq_quant_act, prq_gemm) and X W^T is computed on the device
- * from the bf16 inputs with float32 accumulation.
+ * device with the same bits, then prq_pack_weight, prq_quant_act, prq_gemm) and
+ * X W^T is computed on the device from the bf16 inputs with float32 accumulation.
  *   W_bf16 [N, K], Xcal_bf16 [T, K], X_bf16 [M, K]: host arrays (bf16 bits)
  *   nrmse: host double
  * Allocates and frees its own device buffers, runs on `stream` and

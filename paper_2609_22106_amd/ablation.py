@@ -1,8 +1,8 @@
 """Synthetic ablation grid of Sec. Ablation Studies on the device path.
 
 Every variant that keeps the contiguous tail is evaluated with
-``prq_evaluate_nrmse`` (host export, then pack, act-quant and GEMM on the
-GPU): plain MXFP4 (no scaling, k = 0), PRQuant, w/o AWQ (no scaling), w/o Res
+``prq_evaluate_nrmse`` (export, pack, act-quant and GEMM on the GPU): plain
+MXFP4 (no scaling, k = 0), PRQuant, w/o AWQ (no scaling), w/o Res
 (k = 0) and E8M0-W (weight-side block-scale search).  The "w/o Perm" variant
 appends the residual of channels scattered among the main blocks, so its
 activation tail is a gather of scattered channels quantized on its own --

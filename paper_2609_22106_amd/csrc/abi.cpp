@@ -412,9 +412,10 @@ int prq_grouped_gemm_ex(const uint8_t* Aq, const uint8_t* Asc, const int32_t* gr
       return launch_status(prq::launch_gemm_stream(Aq, Asc, M_total, group_offsets, E, Wp, Wps, N,
                                                    K_aug, Y, c, nullptr, stream));
   }
-  // Row tiles are per expert: pick the shape from the mean rows per expert
-  // (~256 rows per expert at N = 2048, K + k = 832: 176 us with 256 x 256
-  // tiles, 194 with 128 x 128, 248 with 256 x 128).
+  // Row tiles are per expert: pick the shape from the mean rows per expert (us, 256 x
+  // 256 / 128 x 128 tiles, 128 experts routed evenly, 2048 x 832: 160 rows 103 / 99, 192
+  // 114 / 109, 224 121 / 129, 256 127 / 146; 1536 x 1056: 160 87 / 90, 192 95 / 101, 256
+  // 125 / 129; 1040 x 1536: 192 83.5 / 83.7, 256 105 / 108).
   const int shape = per_group >= 192 ? 0 : 2;
   return launch_status(prq::launch_gemm_tile(Aq, Asc, M_total, group_offsets, E, Wp, Wps, N, K_aug,
                                              Y, shape, stream));

@@ -12,15 +12,19 @@
 // consecutive positions: the 4 lanes of a quad hold one 32-block, whose max is
 // reduced with two DPP quad permutations; a thread writes one 32-bit word of 8
 // nibbles (a wave writes 256 contiguous bytes) and lane 0 of the quad the scale.
-// Two kernels:
+// Four kernels:
 //   * rows kernel (few rows, decode): a thread per unit across many
 //     workgroups; perm and d of its 8 positions live in registers (d is given
 //     in position order); the workgroup's rows are copied whole into LDS
 //     while those entries load, and gathered from LDS.
-//   * LDS kernel (many rows, prefill): a workgroup takes a contiguous range of
-//     rows; a thread keeps the perm and d of its units in registers; each row
-//     is staged into LDS with coalesced 16-byte loads (double-buffered, the
-//     next row already loading into registers) and gathered from LDS.
+//   * LDS kernel (more rows, K < 2048): a workgroup takes a contiguous range of
+//     rows; a thread keeps the perm and d of its units in registers; rows are
+//     staged into LDS through registers with coalesced 16-byte loads
+//     (double-buffered, the next pass already loading) and gathered from LDS.
+//   * copy kernel (more rows, K >= 2048): as that, a row at a time copied into LDS
+//     stages by two waves of their own.
+//   * short-row kernel (many rows, K < 2048): the copy kernel with several rows a
+//     stage.
 // E2M1 encoding uses the hardware FP32->FP4 converter on exactly scaled values.
 #include <hip/hip_runtime.h>
 
@@ -935,8 +939,8 @@ hipError_t launch_act_quant_kernel(const uint16_t* X, int64_t ld_x, int M, int K
     return hipGetLastError();
   }
   const int32_t* goff = grouped ? group_offsets : nullptr;
-  // Long rows (K >= 2048): rows copied into LDS stages; shorter rows: several
-  // rows per pass of the register-staged kernel (measured faster at K = 768).
+  // Long rows (K >= 2048): rows copied into LDS stages; shorter ones several to a stage
+  // where there are many (short_rows), else several per pass of the register-staged kernel.
   if (kernel == 3 || (kernel == 0 && K >= 2048)) {
     if (grouped)
       return launch_dma<true, false>(X, ld_x, M, K, k_tail, inv_scale_pos, perm, goff, G, Aq, Asc,

@@ -28,6 +28,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <mutex>
 
@@ -153,9 +154,9 @@ enum AMode { kARow = 0, kAPacked = 1 };
 // [kBN/16 blocks][1 KiB] | A scales | B scales [kBN/16 tiles][64 dwords].  Codes
 // are in MFMA lane order (block b, lane l: row 16b + l % 16, K part l / 16, 16
 // bytes); row-major A codes instead as 16 rows of 64 bytes, row r's K part p in
-// slot p ^ (r / 2) % 4.  A scales: packed as B; row-major not staged (each wave
-// loads its own into registers).  B scales are the packed weight's dwords of the
-// step's group of four steps (byte j = step 4q+j).
+// slot p ^ (r / 2) % 4.  A scales: packed as B; row-major not in the stage (windows of
+// four steps beside it, aw_lds).  B scales are the packed weight's dwords of the step's
+// group of four steps (byte j = step 4q+j).
 template <int kBM, int kBN, int kAMode>
 struct TileStage {
   static constexpr int kABlk = kBM / 16, kBBlk = kBN / 16;
@@ -1208,12 +1209,13 @@ hipError_t launch_persist_shape(const uint8_t* Ap, const uint8_t* Aps, int M, co
                                 int num_cus, hipStream_t stream) {
   constexpr int kThreads = kWM * kWN * 64;
   auto kernel = gemm_grouped_persist_kernel<kBM, kBN, kWM, kWN, 4>;
-  static int per_cu = 0;   // the kernel's occupancy (gfx950 only: the same on every device)
+  static std::atomic<int> occupancy{0};   // gfx950 only: the same on every device and thread
+  int per_cu = occupancy.load(std::memory_order_relaxed);
   if (per_cu == 0) {
-    int n = 0;
-    const hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, kThreads, 0);
+    const hipError_t err = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, 0);
     if (err != hipSuccess) return err;
-    per_cu = std::max(n, 1);
+    per_cu = std::max(per_cu, 1);
+    occupancy.store(per_cu, std::memory_order_relaxed);
   }
   const int grid = std::max(kXcds, num_cus * per_cu / kXcds * kXcds);
   kernel<<<grid, kThreads, 0, stream>>>(Ap, Aps, M, off, E, Wp, Wps, N, K_aug, Y);

@@ -1274,9 +1274,11 @@ double grouped_time(int bm, int bn, int slots, double launch, double slot, doubl
 // 0.93 of the time each are fewer -- and where its larger tiles, half as many to an
 // XCD's workgroups, don't take a round more: 8 experts of 256 rows, 2048 x 832,
 // 14.8 / 12.3, of 1040 x 1536 18.6 / 13.6; 32 of 256 rows, 1040 x 1536, 1.21x.  The routing
-// is not known here, even routing is taken: with uneven routing wide loses up to 17 %
-// where it gains up to 21 % evenly (128 rows: half of the experts with 0.3 of the
-// rows, 1.10-1.17x the time; 256 rows 0.99-1.07x, 384 on 0.93-0.97x).  (160 x 128 with
+// is not known here, even routing is taken.  With uneven routing (half of the experts with
+// 0.1 or 0.3 of the rows, Zipf with exponents 0.5 and 1) wide takes, of 128 x 128's time,
+// E = 128: 1.02-1.20 at 128 rows (0.79-0.91 evenly), 0.94-1.07 at 256 (0.84-0.91), 0.91-1.00
+// at 384 and 512; over all 660 uneven calls the choice is even with 128 x 128 on average,
+// more than 3 % slower in 40 and 1.31x at worst (8 experts of 512 rows, 2048 x 832).  (160 x 128 with
 // three stages 123.6, 192 x 128 151.8; 96 x 128 118.3, and 40.4 at 64 rows.  One
 // workgroup per tile: 158 with 128 x 128, 167 with 256 x 256, 220 with 256 x 128 before
 // the persistent kernel's 119.)
